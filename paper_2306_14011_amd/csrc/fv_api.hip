@@ -30,6 +30,7 @@ struct fv_ctx {
     double* lamB;
     // fused path
     int path, fseg[3], fwaves[3], fitems[3];   // per Runge-Kutta stage
+    int finit;             // work items of the 3D initial wave-speed kernel
     fvk::FGrid* fgrid[3];  // the fused path's grid description per stage (an FGrid3 in 3D); they differ in seg
     unsigned long long* flam;
     double* fdt;
@@ -66,7 +67,7 @@ struct Layout {
     int64_t faces[3];
     int64_t ncell;
     int max_partial;
-    size_t off_status, off_dt, off_fused, off_partial, off_U1, off_U2, off_F[3], off_R, off_lamA, off_lamB, off_met,
+    size_t off_status, off_dt, off_fused, off_lam, off_partial, off_U1, off_U2, off_F[3], off_R, off_lamA, off_lamB, off_met,
         total;
 };
 
@@ -166,8 +167,10 @@ int validate(const fv_grid_desc* g, Layout* L, char* why) {
     o += 256;
     L->off_dt = o;
     o += 256;
-    L->off_fused = o;   // 3 x 512 B: an FGrid or FGrid3 per stage; lambda at +1536, dt at +1544
+    L->off_fused = o;   // 3 x 512 B: an FGrid or FGrid3 per stage; dt at +1536
     o += 2048;
+    L->off_lam = o;
+    o = align256(o + fvk::lam_bytes(1));
     L->off_partial = o;
     o = align256(o + (size_t)L->max_partial * 8);
     const size_t state = (size_t)L->nvar * L->sv * 8;
@@ -427,8 +430,8 @@ int fv_create(const fv_grid_desc* g, void* workspace, size_t workspace_bytes, vo
     c->lamA = (double*)(base + L.off_lamA);
     c->lamB = (double*)(base + L.off_lamB);
     for (int st = 0; st < 3; ++st) c->fgrid[st] = (fvk::FGrid*)(base + L.off_fused + 512 * st);
-    c->flam = (unsigned long long*)(base + L.off_fused + 1536);
-    c->fdt = (double*)(base + L.off_fused + 1544);
+    c->flam = (unsigned long long*)(base + L.off_lam);
+    c->fdt = (double*)(base + L.off_fused + 1536);
     c->path = FV_PATH_SPLIT;
     if (g->nodes) {
         double* met = (double*)(base + L.off_met);
@@ -436,6 +439,7 @@ int fv_create(const fv_grid_desc* g, void* workspace, size_t workspace_bytes, vo
         c->g.met = met;
     }
     fvk::launch_set_u32(c->status, 0u, c->stream);
+    fvk::launch_lam_reset(c->flam, 1, c->stream);
     if (check_launch_error(c) != FV_OK) {
         snprintf(g_err, 256, "%s", c->err);
         delete c;
@@ -496,11 +500,12 @@ static bool has_walls(const fv_ctx* c) {
 static int fused_step3(fv_ctx* c, double* U, int32_t nsteps, const double* dt_in, double* dt_out) {
     const fvk::FGrid3* const* G = (const fvk::FGrid3* const*)c->fgrid;
     const bool walls = has_walls(c);
-    fvk::launch_fused3d_init(c->fwaves[0], G[0], c->fitems[0], U, c->flam, c->status, c->stream);
+    unsigned long long* first = fvk::lam_first(c->flam, 1);
+    fvk::launch_fused3d_init(G[0], c->finit, U, first, c->status, c->stream);
     for (int32_t s = 0; s < nsteps; ++s) {
         {
             SiteTimer t(c, FV_TIMER_FUSED);
-            fvk::launch_fused3d_stage(0, c->fwaves[0], G[0], c->fitems[0], U, U, c->U1, c->flam, c->fdt,
+            fvk::launch_fused3d_stage(0, c->fwaves[0], G[0], c->fitems[0], U, U, c->U1, s ? c->flam : first, c->fdt,
                                       dt_in ? dt_in + s : nullptr, dt_out ? dt_out + s : nullptr, c->status,
                                       c->stream, c->src, c->g.vol, walls);
         }
@@ -526,11 +531,12 @@ static int fused_step(fv_ctx* c, double* U, int32_t nsteps, const double* dt_in,
     if (nsteps == 0) return FV_OK;
     if (c->g.ndim == 3) return fused_step3(c, U, nsteps, dt_in, dt_out);
     const int walls = c->g.met ? 3 : (c->g.mu > 0.0 ? 2 : (has_walls(c) ? 1 : 0));
-    fvk::launch_fused_init(c->fwaves[0], c->fgrid[0], 1, c->fitems[0], U, c->flam, c->status, c->stream, c->g.met);
+    unsigned long long* first = fvk::lam_first(c->flam, 1);
+    fvk::launch_fused_init(c->fgrid[0], 1, c->fitems[0], U, first, c->status, c->stream, c->g.met);
     for (int32_t s = 0; s < nsteps; ++s) {
         {
             SiteTimer t(c, FV_TIMER_FUSED);
-            fvk::launch_fused_stage(0, c->fwaves[0], c->fgrid[0], 1, c->fitems[0], U, U, c->U1, c->flam, c->fdt,
+            fvk::launch_fused_stage(0, c->fwaves[0], c->fgrid[0], 1, c->fitems[0], U, U, c->U1, s ? c->flam : first, c->fdt,
                                     dt_in ? dt_in + s : nullptr, dt_out ? dt_out + s : nullptr, c->status, nullptr,
                                     c->stream, c->src, walls, c->g.met);
         }
@@ -591,6 +597,7 @@ static int set_fused_stage(fv_ctx* c, int st, int32_t seg, int32_t waves) {
         e = hipMemcpyAsync(c->fgrid[st], &G, sizeof(G), hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         c->fitems[st] = fvk::fused3d_items(G, seg);
+        c->finit = fvk::fused3d_init_items(G);
     } else {
         fvk::FGrid G;
         memset(&G, 0, sizeof(G));

@@ -125,7 +125,7 @@ int validate_batch(int32_t ngrids, const fv_grid_desc* grids, BLayout* L, char* 
     L->off_fgrid = o;
     o = a256(o + sizeof(fvk::FGrid) * ngrids);
     L->off_lam = o;
-    o = a256(o + 8 * (size_t)ngrids);
+    o = a256(o + fvk::lam_bytes(ngrids));
     L->off_dt = o;
     o = a256(o + 8 * (size_t)ngrids);
     L->off_status = o;
@@ -366,7 +366,8 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps) {
         b->graph_timed = timed;
         b->graph_history = b->history;
     }
-    fvk::launch_fused_init(b->waves, b->grids, b->ngrids, b->nitems, U, b->lam, b->status, b->stream);
+    fvk::launch_lam_reset(b->lam, b->ngrids, b->stream);
+    fvk::launch_fused_init(b->grids, b->ngrids, b->nitems, U, b->lam, b->status, b->stream);
     for (int32_t s = 0; s < nsteps;) {
         const bool many = nsteps - s >= GRAPH_STEPS;
         hipError_t e = hipGraphLaunch(many ? b->exec_many : b->exec, b->stream);

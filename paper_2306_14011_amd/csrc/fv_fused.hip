@@ -7,31 +7,40 @@
 
 namespace fvk {
 
-// lambda_max of U^n per grid (the first step's dt), same work items.
+// lambda_max of U^n per grid (the first step's dt), same work items. Bound by
+// the latency of its loads: four rows are read at once.
 __global__ void __launch_bounds__(256) k_fused_lambda(const FGrid* __restrict__ grids, int ngrids, int nitems,
                                                       const double* __restrict__ U, unsigned long long* __restrict__ lam,
                                                       uint32_t* __restrict__ status, const double* __restrict__ met) {
     const int lane = threadIdx.x & 63;
-    const int nwaves = (gridDim.x * blockDim.x) >> 6;
-    const int wave0 = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
-    for (int item = wave0; item < nitems; item += nwaves) {
-        const int gi = find_grid(grids, ngrids, item);
-        const FGrid G = grids[gi];
-        const int local = item - G.work0;
-        const int strip = local % G.strips;
-        const int sidx = local / G.strips;
-        const int col = FW * strip + lane;
-        double lmax = 0.0;
-        uint32_t fl = 0;
-        if (lane < FW && col < G.nx) {
-            const double idx[2] = {G.inv_dx, G.inv_dy};
-            for (int rr = sidx * G.seg; rr < sidx * G.seg + G.seg && rr < G.ny; ++rr) {
-                const long long p = G.base + (long long)rr * G.pitch + col;
-                double q[4];
+    const int item = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+    if (item >= nitems) return;
+    const FGrid G = grids[find_grid(grids, ngrids, item)];
+    const int local = item - G.work0;
+    const int strip = local % G.strips;
+    const int sidx = local / G.strips;
+    const int col = FW * strip + lane;
+    double lmax = 0.0;
+    uint32_t fl = 0;
+    if (lane < FW && col < G.nx) {
+        const double idx[2] = {G.inv_dx, G.inv_dy};
+        const int r0 = sidx * G.seg, r1 = r0 + G.seg < G.ny ? r0 + G.seg : G.ny;
+        for (int rb = r0; rb < r1; rb += 4) {
+            double q[4][4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) q[v] = U[v * G.sv + p];
-                double lam = cell_lambda<2>(q, G.gamma, G.gm1, idx, fl);
-                if (G.mu > 0.0) lam += 2.0 * ((G.mu / q[0]) * G.nu_fac) * (G.inv_dx * G.inv_dx + G.inv_dy * G.inv_dy);
+            for (int k = 0; k < 4; ++k) {
+                // rows past the segment read its last row again
+                const int rr = rb + k < r1 ? rb + k : r1 - 1;
+                const long long p = G.base + (long long)rr * G.pitch + col;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) q[k][v] = U[v * G.sv + p];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int rr = rb + k < r1 ? rb + k : r1 - 1;
+                double lam = cell_lambda<2>(q[k], G.gamma, G.gm1, idx, fl);
+                if (G.mu > 0.0)
+                    lam += 2.0 * ((G.mu / q[k][0]) * G.nu_fac) * (G.inv_dx * G.inv_dx + G.inv_dy * G.inv_dy);
                 if (met) {
                     // curvilinear: the faces' unit normals and lengths, the cell's area
                     const MetricOffsets mo = metric_offsets(G.nx, G.ny);
@@ -39,29 +48,29 @@ __global__ void __launch_bounds__(256) k_fused_lambda(const FGrid* __restrict__ 
                     const long long fx = (long long)rr * (G.nx + 1) + col;
                     double xa[3], xb[3], ya[3], yb[3];
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        xa[k] = met[mo.fx + k * mo.nfx + fx];
-                        xb[k] = met[mo.fx + k * mo.nfx + fx + 1];
-                        ya[k] = met[mo.fy + k * mo.nfy + e];
-                        yb[k] = met[mo.fy + k * mo.nfy + e + G.nx];
+                    for (int m = 0; m < 3; ++m) {
+                        xa[m] = met[mo.fx + m * mo.nfx + fx];
+                        xb[m] = met[mo.fx + m * mo.nfx + fx + 1];
+                        ya[m] = met[mo.fy + m * mo.nfy + e];
+                        yb[m] = met[mo.fy + m * mo.nfy + e + G.nx];
                     }
-                    lam = curv_cell_lambda(q, G.gamma, G.gm1, xa, xb, ya, yb, met[mo.cell + e]);
+                    lam = curv_cell_lambda(q[k], G.gamma, G.gm1, xa, xb, ya, yb, met[mo.cell + e]);
                 }
                 lmax = fmax(lmax, lam);
             }
         }
-        lmax = wave_max_d(lmax);
-        fl = wave_or(fl);
-        if (lane == 0) {
-            atomicMax(&lam[G.gid], (unsigned long long)__double_as_longlong(lmax));
-            if (fl) atomicOr(status, fl);
-        }
+    }
+    lmax = wave_max_d(lmax);
+    fl = wave_or(fl);
+    if (lane == 0) {
+        lam_add(lam, G.gid, item, lmax);
+        if (fl) atomicOr(status, fl);
     }
 }
 
 // Zero the lambda accumulators.
-__global__ void k_fused_reset(unsigned long long* lam, int ngrids) {
-    for (int g = threadIdx.x; g < ngrids; g += blockDim.x) lam[g] = 0ull;
+__global__ void k_lam_reset(unsigned long long* lam, int ngrids) {
+    lam_clear(lam, ngrids, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -96,10 +105,15 @@ void launch_fused_stage(int stage, int waves, const FGrid* grids, int ngrids, in
 #undef FV_LFS
 }
 
-void launch_fused_init(int waves, const FGrid* grids, int ngrids, int nitems, const double* U,
-                       unsigned long long* lam, uint32_t* status, hipStream_t s, const double* met) {
-    hipLaunchKernelGGL(k_fused_reset, dim3(1), dim3(256), 0, s, lam, ngrids);
-    const dim3 grid(fused_blocks(nitems, waves)), block(256);
+void launch_lam_reset(unsigned long long* lam, int ngrids, hipStream_t s) {
+    const int n = 2 * ngrids * LAM_SLOTS;
+    hipLaunchKernelGGL(k_lam_reset, dim3((n + 255) / 256), dim3(256), 0, s, lam, ngrids);
+}
+
+// lam: cleared slots.
+void launch_fused_init(const FGrid* grids, int ngrids, int nitems, const double* U, unsigned long long* lam,
+                       uint32_t* status, hipStream_t s, const double* met) {
+    const dim3 grid(fused_blocks(nitems, 0)), block(256);
     hipLaunchKernelGGL(k_fused_lambda, grid, block, 0, s, grids, ngrids, nitems, U, lam, status, met);
 }
 

@@ -22,7 +22,8 @@
 // Per-grid dt: stage 1 computes dt = cfl / lambda_max(U^n) from the max that
 // the previous step's stage 3 (or the init kernel) accumulated; stage 2
 // resets the accumulator; stage 3 accumulates lambda_max(U^{n+1}) with an
-// atomic max on the bit pattern of the (non-negative) double.
+// atomic max on the bit pattern of the (non-negative) double, spread over the
+// grid's slots (lam_index).
 //
 // The kernel template lives in this header so that the curvilinear variant
 // can be instantiated in a source of its own, built with multiply-add
@@ -500,8 +501,7 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
     const int nwaves = (gridDim.x * blockDim.x) >> 6;
     const int wave0 = __builtin_amdgcn_readfirstlane(
         (int)((xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 6));
-    if (STAGE == 1 && blockIdx.x == 0)
-        for (int g = threadIdx.x; g < ngrids; g += blockDim.x) lam[g] = 0ull;  // stage 1 has read it
+    if (STAGE == 1 && blockIdx.x == 0) lam_clear(lam, ngrids, threadIdx.x, blockDim.x);  // stage 1 has read it
     for (int item = wave0; item < nitems; item += nwaves) {
         unsigned long long t_start = 0;
         if (clk) t_start = wall_clock64();
@@ -512,7 +512,7 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
         const int sidx = local / G.strips;
         double dt;
         if (STAGE == 0) {
-            dt = dt_fixed ? dt_fixed[G.gid] : G.cfl / __longlong_as_double((long long)lam[G.gid]);
+            dt = dt_fixed ? dt_fixed[G.gid] : G.cfl / lam_read(lam, G.gid, lane);
             if (local == 0 && lane == 0) {
                 dtg[G.gid] = dt;
                 if (dt_out) dt_out[G.gid] = dt;
@@ -539,7 +539,7 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
             lmax = wave_max_d(lmax);
             fl = wave_or(fl);
             if (lane == 0) {
-                atomicMax(&lam[G.gid], (unsigned long long)__double_as_longlong(lmax));
+                lam_add(lam, G.gid, item, lmax);
                 if (fl) atomicOr(status, fl);
             }
         }

@@ -360,14 +360,14 @@ __global__ void __launch_bounds__(T3) __attribute__((amdgpu_waves_per_eu(2))) k_
     const int lane = tid & 63;
     const int nblocks = gridDim.x;
     const int b0 = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
-    if (STAGE == 1 && blockIdx.x == 0 && tid == 0) lam[0] = 0ull;  // stage 1 has read it
+    if (STAGE == 1 && blockIdx.x == 0) lam_clear(lam, 1, tid, T3);  // stage 1 has read it
     const FGrid3 G = *grid;
     for (int item = b0; item < nitems; item += nblocks) {
         int tx0, ty0, k0;
         tile_of_item(G, item, tx0, ty0, k0);
         double dt;
         if (STAGE == 0) {
-            dt = dt_fixed ? dt_fixed[0] : G.cfl / __longlong_as_double((long long)lam[0]);
+            dt = dt_fixed ? dt_fixed[0] : G.cfl / lam_read(lam, 0, lane);
             if (item == 0 && tid == 0) {
                 dtg[0] = dt;
                 if (dt_out) dt_out[0] = dt;
@@ -394,47 +394,52 @@ __global__ void __launch_bounds__(T3) __attribute__((amdgpu_waves_per_eu(2))) k_
             lmax = wave_max_d(lmax);
             fl = wave_or(fl);
             if (lane == 0) {
-                atomicMax(&lam[0], (unsigned long long)__double_as_longlong(lmax));
+                lam_add(lam, 0, 4 * item + (tid >> 6), lmax);
                 if (fl) atomicOr(status, fl);
             }
         }
     }
 }
 
-// lambda_max of U^n (the first step's dt), over the same work items.
-__global__ void __launch_bounds__(T3) k_fused3d_lambda(const FGrid3* __restrict__ grid, int nitems,
-                                                       const double* __restrict__ U,
+// lambda_max of U^n (the first step's dt), over the same tiles, LAM_PLANES
+// planes per workgroup: many short workgroups, since the kernel is bound by
+// the latency of its loads.
+constexpr int LAM_PLANES = 4;
+__global__ void __launch_bounds__(T3) k_fused3d_lambda(const FGrid3* __restrict__ grid, const double* __restrict__ U,
                                                        unsigned long long* __restrict__ lam,
                                                        uint32_t* __restrict__ status) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const FGrid3 G = *grid;
-    for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
-        int tx0, ty0, k0;
-        tile_of_item(G, item, tx0, ty0, k0);
-        const int gx = tx0 + tid % TX, gy = ty0 + tid / TX;
-        double lmax = 0.0;
-        uint32_t fl = 0;
-        if (tid < TCELLS && gx < G.nx && gy < G.ny) {
-            const double idx[3] = {G.inv_dx, G.inv_dy, G.inv_dz};
-            for (int kk = k0; kk < k0 + G.seg && kk < G.nz; ++kk) {
-                const long long p = G.base + (long long)kk * G.pz + (long long)gy * G.py + gx;
-                double q[5];
+    const int item = blockIdx.x;
+    const int tiles_x = (G.nx + TX - 1) / TX, tiles_y = (G.ny + TY - 1) / TY;
+    const int r = item / tiles_x;
+    const int gx = (item % tiles_x) * TX + tid % TX, gy = (r % tiles_y) * TY + tid / TX;
+    const int k0 = (r / tiles_y) * LAM_PLANES;
+    double lmax = 0.0;
+    uint32_t fl = 0;
+    if (tid < TCELLS && gx < G.nx && gy < G.ny) {
+        const double idx[3] = {G.inv_dx, G.inv_dy, G.inv_dz};
+        double q[LAM_PLANES][5];
 #pragma unroll
-                for (int v = 0; v < 5; ++v) q[v] = U[v * G.sv + p];
-                lmax = fmax(lmax, cell_lambda<3>(q, G.gamma, G.gm1, idx, fl));
-            }
+        for (int k = 0; k < LAM_PLANES; ++k) {
+            // planes past the grid read its last plane again
+            const int kk = k0 + k < G.nz ? k0 + k : G.nz - 1;
+            const long long p = G.base + (long long)kk * G.pz + (long long)gy * G.py + gx;
+#pragma unroll
+            for (int v = 0; v < 5; ++v) q[k][v] = U[v * G.sv + p];
         }
-        lmax = wave_max_d(lmax);
-        fl = wave_or(fl);
-        if (lane == 0) {
-            atomicMax(&lam[0], (unsigned long long)__double_as_longlong(lmax));
-            if (fl) atomicOr(status, fl);
-        }
+#pragma unroll
+        for (int k = 0; k < LAM_PLANES; ++k)
+            lmax = fmax(lmax, cell_lambda<3>(q[k], G.gamma, G.gm1, idx, fl));
+    }
+    lmax = wave_max_d(lmax);
+    fl = wave_or(fl);
+    if (lane == 0) {
+        lam_add(lam, 0, 4 * item + (tid >> 6), lmax);
+        if (fl) atomicOr(status, fl);
     }
 }
-
-__global__ void k_fused3d_reset(unsigned long long* lam) { lam[0] = 0ull; }
 
 // ---------------------------------------------------------------------------
 
@@ -486,12 +491,13 @@ void launch_fused3d_stage(int stage, int waves, const FGrid3* grid, int nitems, 
     }
 }
 
-void launch_fused3d_init(int waves, const FGrid3* grid, int nitems, const double* U, unsigned long long* lam,
-                         uint32_t* status, hipStream_t s) {
-    hipLaunchKernelGGL(k_fused3d_reset, dim3(1), dim3(1), 0, s, lam);
-    hipLaunchKernelGGL(k_fused3d_lambda, dim3(blocks_for(nitems, waves)), dim3(T3), 0, s, grid, nitems, U, lam,
-                       status);
+// lam: cleared slots. nitems: the tiles times segments of LAM_PLANES planes.
+void launch_fused3d_init(const FGrid3* grid, int nitems, const double* U, unsigned long long* lam, uint32_t* status,
+                         hipStream_t s) {
+    hipLaunchKernelGGL(k_fused3d_lambda, dim3(nitems), dim3(T3), 0, s, grid, U, lam, status);
 }
+
+int fused3d_init_items(const FGrid3& G) { return fused3d_items(G, LAM_PLANES); }
 
 // Workgroups the device holds at once for the stage kernels.
 int fused3d_slots() {

@@ -43,16 +43,49 @@ __device__ __forceinline__ int find_grid(const FGrid* __restrict__ grids, int ng
     return lo;
 }
 
+// Maximum over the wave of non-negative values, uniform: DPP row shifts and
+// row broadcasts gather it in lane 63 (a lane without a source takes 0), no
+// LDS round trips.
+template <int CTRL>
+__device__ __forceinline__ double dpp_max(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return fmax(v, __longlong_as_double(((long long)hi << 32) | (unsigned int)lo));
+}
+
 __device__ __forceinline__ double wave_max_d(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
+    v = dpp_max<0x111>(v);  // row_shr:1, 2, 4, 8: the row's maximum in its last lane
+    v = dpp_max<0x112>(v);
+    v = dpp_max<0x114>(v);
+    v = dpp_max<0x118>(v);
+    v = dpp_max<0x142>(v);  // row_bcast:15
+    v = dpp_max<0x143>(v);  // row_bcast:31
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, 63);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
 __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v |= __shfl_xor(v, off, 64);
     return v;
+}
+
+// The grid's maximum over the slots (every lane gets it).
+__device__ __forceinline__ double lam_read(const unsigned long long* lam, int grid, int lane) {
+    return wave_max_d(__longlong_as_double((long long)lam[lam_index(grid, lane & (LAM_SLOTS - 1))]));
+}
+
+// Adds a wave's maximum (lane 0's) to the slot of its work item.
+__device__ __forceinline__ void lam_add(unsigned long long* lam, int grid, int item, double lmax) {
+    atomicMax(&lam[lam_index(grid, item & (LAM_SLOTS - 1))], (unsigned long long)__double_as_longlong(lmax));
+}
+
+// Clears the slots of both sets of ngrids grids with the threads t of nt.
+__device__ __forceinline__ void lam_clear(unsigned long long* lam, int ngrids, int t, int nt) {
+    for (int i = t; i < 2 * ngrids * LAM_SLOTS; i += nt) lam[i * LAM_PAD] = 0ull;
 }
 
 // Buffer access with a wave-uniform descriptor (the grid's array), a per-lane

@@ -15,6 +15,21 @@ constexpr int CLK_SLOTS = 16;
 constexpr int CLK_PAD = 16;  // unsigned long longs per slot (one 128-byte line)
 __host__ __device__ inline int clk_index(int entry, int slot) { return (entry * CLK_SLOTS + slot) * CLK_PAD; }
 
+// Wave-speed maximum of a grid (bit patterns of non-negative doubles), spread
+// over LAM_SLOTS slots a 256-byte line apart that waves pick by their work
+// item: device-scope atomics on one address cost about 10 ns each, one after
+// the other, and the waves of a stage end together (512^2: 1152 of them made
+// the last stage 23.4 us against 11.5 for the one before; over the slots it
+// takes 12). The reader takes the maximum of the slots, one per lane. Two
+// sets per grid: the stage kernels accumulate in set 0, the wave speed of a
+// call's first state goes to set 1; the second stage clears both, so a call
+// needs no clearing launch of its own.
+constexpr int LAM_SLOTS = 32;
+constexpr int LAM_PAD = 32;  // unsigned long longs per slot (256 bytes)
+__host__ __device__ inline int lam_index(int grid, int slot) { return (grid * LAM_SLOTS + slot) * LAM_PAD; }
+inline size_t lam_bytes(int ngrids) { return (size_t)2 * ngrids * LAM_SLOTS * LAM_PAD * 8; }
+inline unsigned long long* lam_first(unsigned long long* lam, int ngrids) { return lam + lam_index(ngrids, 0); }
+
 struct FGrid {
     int nx, ny, pitch, strips, work0, scheme;  // scheme: FV_SCHEME_*
     int bcx0, bcx1, bcy0, bcy1, gid, seg;   // gid: the caller's grid index (slots of lam, dt, clocks);
@@ -63,17 +78,19 @@ void launch_fused_stage(int stage, int waves, const FGrid* grids, int ngrids, in
                         const double* Us, double* Ud, unsigned long long* lam, double* dtg, const double* dt_fixed,
                         double* dt_out, uint32_t* status, unsigned long long* clk, hipStream_t s,
                         const double* src = nullptr, int mode = 0, const double* met = nullptr);
-void launch_fused_init(int waves, const FGrid* grids, int ngrids, int nitems, const double* U,
-                       unsigned long long* lam, uint32_t* status, hipStream_t s, const double* met = nullptr);
+void launch_lam_reset(unsigned long long* lam, int ngrids, hipStream_t s);
+void launch_fused_init(const FGrid* grids, int ngrids, int nitems, const double* U, unsigned long long* lam,
+                       uint32_t* status, hipStream_t s, const double* met = nullptr);
 int fused_slots();
 int fused3d_items(const FGrid3& G, int seg);
 void launch_fused3d_stage(int stage, int waves, const FGrid3* grid, int nitems, const double* Un, const double* Us,
                           double* Ud, unsigned long long* lam, double* dtg, const double* dt_fixed, double* dt_out,
                           uint32_t* status, hipStream_t s, const double* src = nullptr, double vol = 0.0,
                           bool walls = false);
-void launch_fused3d_init(int waves, const FGrid3* grid, int nitems, const double* U, unsigned long long* lam,
+void launch_fused3d_init(const FGrid3* grid, int nitems, const double* U, unsigned long long* lam,
                          uint32_t* status, hipStream_t s);
 int fused3d_slots();
+int fused3d_init_items(const FGrid3& G);
 int fused3d_auto_seg(const FGrid3& G, int slots);
 int fused_auto_seg(const FGrid* grids, int ngrids, int slots);
 
