@@ -521,7 +521,8 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
         } else {
             dt = dtg[G.gid];
         }
-        const double s = MODE == 3 ? -dt : -dt * G.inv_vol;  // curvilinear: times each cell's 1 / area
+        // curvilinear: times each cell's 1 / area; held in scalar registers
+        const double s = from_lane(MODE == 3 ? -dt : -dt * G.inv_vol, 0);
         double lmax = 0.0;
         uint32_t fl = 0;
         if (G.scheme == 0) {

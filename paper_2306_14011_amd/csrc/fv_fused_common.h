@@ -54,17 +54,21 @@ __device__ __forceinline__ double dpp_max(double v) {
     return fmax(v, __longlong_as_double(((long long)hi << 32) | (unsigned int)lo));
 }
 
+// Lane l's value, uniform.
+__device__ __forceinline__ double from_lane(double v, int l) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, l);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
 __device__ __forceinline__ double wave_max_d(double v) {
     v = dpp_max<0x111>(v);  // row_shr:1, 2, 4, 8: the row's maximum in its last lane
     v = dpp_max<0x112>(v);
     v = dpp_max<0x114>(v);
     v = dpp_max<0x118>(v);
     v = dpp_max<0x142>(v);  // row_bcast:15
-    v = dpp_max<0x143>(v);  // row_bcast:31
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)b, 63);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+    return from_lane(dpp_max<0x143>(v), 63);  // row_bcast:31
 }
 
 __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
