@@ -91,10 +91,20 @@ __device__ __forceinline__ void visc_flux2(const double* wa, const double* wb, c
 // drops them. A conditional load or store would make the compiler's wait
 // counting assume the shortest path and wait for every outstanding access
 // (the prefetches included) at the top of each row.
+//
+// gq: the grid's inflow states in its table entry, q[axis][side][variable].
+// The boundary and viscous variants read them where a ghost cell takes one,
+// under one uniform branch per row that nearly all rows skip: held in scalar
+// registers with the rest of the table entry they cost up to 165 scalar
+// spills into vector registers and two selects per variable and side in every
+// row (viscous 1024^2: 694 us for 6 steps against 607; the inlet channel
+// 403x277: 253 against 247 us for 8). The curvilinear variant, bound by its
+// reads, ran 3-5% slower with the branch and keeps the selects.
 template <int STAGE, int LIM, bool SRC, int MODE>
-__device__ __forceinline__ void fused2d_rows(const FGrid& G, int lane, int strip, int r0, double s, const double* Un,
-                                             const double* Us, double* Ud, double& lmax, uint32_t& fl, double ka,
-                                             double kb, const double* src, const double* met) {
+__device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* __restrict__ gq, int lane, int strip, int r0,
+                                             double s, const double* Un, const double* Us, double* Ud, double& lmax,
+                                             uint32_t& fl, double ka, double kb, const double* src,
+                                             const double* met) {
     constexpr bool BC = MODE >= 1;     // boundary variant: slip walls and inflow faces
     constexpr bool VISC = MODE == 2;   // and the viscous flux
     constexpr bool CURV = MODE == 3;   // or a curvilinear grid (metric streams)
@@ -111,6 +121,18 @@ __device__ __forceinline__ void fused2d_rows(const FGrid& G, int lane, int strip
     // side's given state), per lane; -1 inside the grid
     const int xk = !BC ? -1 : (col < 0 ? G.bcx0 : (col >= G.nx ? G.bcx1 : -1));
     const int xside = col < 0 ? 0 : 1;
+    // curvilinear variant: the inflow states, read here with constant indices
+    // and picked by selects (a run-time index into a local copy would move it
+    // to scratch memory)
+    double q[2][2][4];
+    if (CURV) {
+#pragma unroll
+        for (int a = 0; a < 16; ++a) q[a >> 3][(a >> 2) & 1][a & 3] = gq[a];
+    }
+    // whether any lane of the strip has a ghost column behind a wall or an
+    // inflow face (uniform): the other strips skip the column rules
+    const bool xwall = BC && __ballot(xk == 2) != 0;
+    const bool xflow = BC && __ballot(xk == 3) != 0;
     // curvilinear variant: the metric streams (unit normal x, y and length of
     // the x faces, the same of the y faces, cell area and 1 / area) through
     // one descriptor per block, this lane's face and cell columns clamped
@@ -142,13 +164,6 @@ __device__ __forceinline__ void fused2d_rows(const FGrid& G, int lane, int strip
     };
     auto my_row = [&](int r) { return (uint32_t)((long long)(r < 0 ? 0 : (r > G.ny ? G.ny : r)) * G.nx * 8); };
     auto mc_row = [&](int r) { return (uint32_t)((long long)(r < 0 ? 0 : (r > G.ny - 1 ? G.ny - 1 : r)) * G.nx * 8); };
-    // a slip wall's mirror cell with its velocity reflected about the wall
-    // face's unit normal (nx, ny): m - 2 (m . n) n
-    auto reflect = [&](double* w, double nx, double ny) {
-        const double mn = w[1] * nx + w[2] * ny;
-        w[1] -= 2.0 * mn * nx;
-        w[2] -= 2.0 * mn * ny;
-    };
     // curvilinear variant: the unit normal of row r's x wall face on this lane's side
     auto wall_normal = [&](int r, double* wn) {
         if (!CURV) return;
@@ -157,31 +172,55 @@ __device__ __forceinline__ void fused2d_rows(const FGrid& G, int lane, int strip
     };
     // applies the ghost rules of row r (uniform) and of this lane's column to a
     // loaded cell (wn: the row's x wall normal, curvilinear variant)
-    auto ghost = [&](double* w, int r, const double* wn) {
+    // (worked on in locals with constant indices and written back once: stores
+    // to the row under the rules' branches moved the window to scratch memory)
+    auto ghost = [&](double* w, int r, const double* wn) __attribute__((always_inline)) {
         if (!BC) return;
         const int yk = r < 0 ? G.bcy0 : (r >= G.ny ? G.bcy1 : -1);
         const int ys = r < 0 ? 0 : 1;
-        // (the side indices select between constant indices: indexing the
-        // kernel's local copy of the grid table, or a local array, with a
-        // run-time index would move it to scratch memory)
-        if (yk == 2) {
-            if (CURV) reflect(w, ys ? wyn[1][0] : wyn[0][0], ys ? wyn[1][1] : wyn[0][1]);
-            else w[2] = -w[2];
-        }
-        if (yk == 3) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) w[v] = ys ? G.q[1][1][v] : G.q[1][0][v];
-        }
         if (CURV) {
-            double m[NV] = {w[0], w[1], w[2], w[3]};
-            reflect(m, wn[0], wn[1]);
-            w[1] = xk == 2 ? m[1] : w[1];
-            w[2] = xk == 2 ? m[2] : w[2];
-        } else {
-            w[1] = xk == 2 ? -w[1] : w[1];
-        }
+            // a slip wall's mirror cell has its velocity reflected about the
+            // wall face's unit normal n: m - 2 (m . n) n
+            if (yk == 2) {
+                const double nx = ys ? wyn[1][0] : wyn[0][0], ny = ys ? wyn[1][1] : wyn[0][1];
+                const double mn = w[1] * nx + w[2] * ny;
+                w[1] -= 2.0 * mn * nx;
+                w[2] -= 2.0 * mn * ny;
+            }
+            if (yk == 3) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) w[v] = xk == 3 ? (xside ? G.q[0][1][v] : G.q[0][0][v]) : w[v];
+                for (int v = 0; v < NV; ++v) w[v] = ys ? q[1][1][v] : q[1][0][v];
+            }
+            const double mn = w[1] * wn[0] + w[2] * wn[1];
+            const double m1 = w[1] - 2.0 * mn * wn[0], m2 = w[2] - 2.0 * mn * wn[1];
+            w[1] = xk == 2 ? m1 : w[1];
+            w[2] = xk == 2 ? m2 : w[2];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) w[v] = xk == 3 ? (xside ? q[0][1][v] : q[0][0][v]) : w[v];
+            return;
+        }
+        if (!(xwall || xflow || yk >= 2)) return;
+        double m0 = w[0], m1 = w[1], m2 = w[2], m3 = w[3];
+        if (yk == 2) m2 = -m2;
+        if (yk == 3) {
+            m0 = gq[(2 + ys) * 4];
+            m1 = gq[(2 + ys) * 4 + 1];
+            m2 = gq[(2 + ys) * 4 + 2];
+            m3 = gq[(2 + ys) * 4 + 3];
+        }
+        if (xwall) m1 = xk == 2 ? -m1 : m1;
+        if (xflow) {
+            const double* qs = gq + xside * 4;
+            const double q0 = qs[0], q1 = qs[1], q2 = qs[2], q3 = qs[3];
+            m0 = xk == 3 ? q0 : m0;
+            m1 = xk == 3 ? q1 : m1;
+            m2 = xk == 3 ? q2 : m2;
+            m3 = xk == 3 ? q3 : m3;
+        }
+        w[0] = m0;
+        w[1] = m1;
+        w[2] = m2;
+        w[3] = m3;
     };
     const bool out_lane = lane >= 2 && lane < 2 + FW && col < G.nx;
     const long long gbytes = 4 * G.sv * 8;  // one grid's state, below 4 GiB
@@ -323,10 +362,10 @@ __device__ __forceinline__ void fused2d_rows(const FGrid& G, int lane, int strip
             const int t = (j + 1) & 3;  // f mod 4, a compile-time constant
             const int rr = r0 + f - 1;  // output row finished at this face
             // rows rr-1 .. rr+2 sit in slots t .. t+3; row rr-1 is no longer
-            // needed, so its slot takes row rr + 3 (for face f + 1) right away
-            // row rr + 2, loaded one row ago, takes its ghost rules here, where
+            // needed, so its slot takes row rr + 3 (for face f + 1) right away.
+            // Row rr + 2, loaded one row ago, takes its ghost rules here, where
             // it is first used: applied at the load, they would make the row
-            // wait for its own loads
+            // wait for its own loads (after this row's loads measured slower)
             ghost(W[(t + 3) & 3], rr + 2, wxp);
             double c[NV];
 #pragma unroll
@@ -506,7 +545,8 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
         unsigned long long t_start = 0;
         if (clk) t_start = wall_clock64();
         const int gi = find_grid(grids, ngrids, item);
-        const FGrid G = grids[gi];
+        const FGridHead G = grids[gi];
+        const double* gq = &grids[gi].q[0][0][0];
         const int local = item - G.work0;
         const int strip = local % G.strips;
         const int sidx = local / G.strips;
@@ -526,15 +566,15 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
         double lmax = 0.0;
         uint32_t fl = 0;
         if (G.scheme == 0) {
-            fused2d_rows<STAGE, 0, SRC, MODE>(G, lane, strip, sidx * G.seg, s, Un, Us, Ud, lmax, fl, 0.0, 0.0, src, met);
+            fused2d_rows<STAGE, 0, SRC, MODE>(G, gq, lane, strip, sidx * G.seg, s, Un, Us, Ud, lmax, fl, 0.0, 0.0, src, met);
         } else if (G.scheme == 5) {
-            fused2d_rows<STAGE, 3, SRC, MODE>(G, lane, strip, sidx * G.seg, s, Un, Us, Ud, lmax, fl, 0.0, 0.0, src, met);
+            fused2d_rows<STAGE, 3, SRC, MODE>(G, gq, lane, strip, sidx * G.seg, s, Un, Us, Ud, lmax, fl, 0.0, 0.0, src, met);
         } else if (G.scheme == 1) {
-            fused2d_rows<STAGE, 1, SRC, MODE>(G, lane, strip, sidx * G.seg, s, Un, Us, Ud, lmax, fl, 0.0, 0.0, src, met);
+            fused2d_rows<STAGE, 1, SRC, MODE>(G, gq, lane, strip, sidx * G.seg, s, Un, Us, Ud, lmax, fl, 0.0, 0.0, src, met);
         } else {
             double ka, kb;
             kappa_weights(G.scheme, ka, kb);
-            fused2d_rows<STAGE, 2, SRC, MODE>(G, lane, strip, sidx * G.seg, s, Un, Us, Ud, lmax, fl, ka, kb, src, met);
+            fused2d_rows<STAGE, 2, SRC, MODE>(G, gq, lane, strip, sidx * G.seg, s, Un, Us, Ud, lmax, fl, ka, kb, src, met);
         }
         if (STAGE == 2) {
             lmax = wave_max_d(lmax);

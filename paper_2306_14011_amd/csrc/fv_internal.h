@@ -30,7 +30,8 @@ __host__ __device__ inline int lam_index(int grid, int slot) { return (grid * LA
 inline size_t lam_bytes(int ngrids) { return (size_t)2 * ngrids * LAM_SLOTS * LAM_PAD * 8; }
 inline unsigned long long* lam_first(unsigned long long* lam, int ngrids) { return lam + lam_index(ngrids, 0); }
 
-struct FGrid {
+// (FGridHead: what the kernels keep in scalar registers.)
+struct FGridHead {
     int nx, ny, pitch, strips, work0, scheme;  // scheme: FV_SCHEME_*
     int bcx0, bcx1, bcy0, bcy1, gid, seg;   // gid: the caller's grid index (slots of lam, dt, clocks);
                                             // seg: rows per work item (a multiple of 4)
@@ -38,19 +39,25 @@ struct FGrid {
     long long sv;       // per-variable stride
     double ax, ay;      // face areas of x faces (dy) and y faces (dx)
     double inv_vol, inv_dx, inv_dy, cfl, gamma, gm1;
-    double q[2][2][4];  // conserved ghost state of inflow faces per axis and side (the kernels'
-                        // boundary variant only: grids with slip walls or inflow faces)
     double mu, kcond, nu_fac;  // viscosity, heat conductivity, max(4/3, gamma / Pr) (viscous variant)
 };
 
+struct FGrid : FGridHead {
+    double q[2][2][4];  // conserved ghost state of inflow faces per axis and side (the kernels'
+                        // boundary variant only: grids with slip walls or inflow faces)
+};
+
 // The 3D grid of the fused path (device memory, read uniformly).
-struct FGrid3 {
+struct FGrid3Head {
     int nx, ny, nz, strips, seg, scheme;       // seg: planes per work item (a multiple of 4)
     int bcx0, bcx1, bcy0, bcy1, bcz0, bcz1;
     long long base;                                // element offset of cell (0,0,0), variable 0
     long long sv, py, pz;                          // strides: variable, row (y), plane (z)
     double ax, ay, az;                             // face areas: dy dz, dx dz, dx dy
     double inv_vol, inv_dx, inv_dy, inv_dz, cfl, gamma, gm1;
+};
+
+struct FGrid3 : FGrid3Head {
     double q[3][2][5];  // conserved ghost state of inflow faces per axis and side (boundary variant)
 };
 
