@@ -201,97 +201,95 @@ __host__ __device__ __forceinline__ void muscl(double q0, double q1, double q2, 
     }
 }
 
+// x with its sign bit set where r's is: a negative density makes the product
+// of the two densities negative whatever the other's sign, so that its root
+// is NaN and the flux carries it.
+__host__ __device__ __forceinline__ double sign_from(double x, double r) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const long long b = __double_as_longlong(x), n = __double_as_longlong(r);
+    const uint32_t hi = (uint32_t)(b >> 32) | ((uint32_t)(n >> 32) & 0x80000000u);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | (uint32_t)b));
+#else
+    return r < 0.0 ? -fabs(x) : x;
+#endif
+}
+
 // Roe flux along axis AX for NDIM dimensions, conserved face states in, flux out.
 // F = (F(qL) + F(qR))/2 - sum_k |lambda_k| alpha_k r_k / 2, no entropy fix.
 // TWICE returns 2F: callers that difference the fluxes fold the exact factor
 // 1/2 into their face areas and save a multiply per component.
+//
+// The vector ALU bounds every kernel that evaluates it, so the operations are
+// counted: 86 in 2D, 3 of them reciprocal estimates at a quarter of the rate
+// (102 with 4 estimates when written by wave strengths).
+//  - One root serves both densities: with y = (rL rR)^(-1/2), 1/rL = rR y^2,
+//    1/rR = rL y^2, the averaged density is rL rR y, and the Roe weight of the
+//    right state is sqrt(rR) / (sqrt(rL) + sqrt(rR)) = rR / (rR + rho~).
+//  - The dissipation is |u_n| dU plus an acoustic part. With m = min(|u_n| / c, 1)
+//    (the two acoustic speeds' half sum is max(|u_n|, c), their half difference
+//    u_n clamped to +-c), s = m with u_n's sign and t = c (1 - m):
+//      A = (t / c^2) dp + s rho~ du_n,  B = s dp + t rho~ du_n  (t / c^2 = (1 - m) / c),
+//      D = |u_n| dU + A (1, u~, H~) + B (0, n, u~_n).
+// Fused multiply-adds are written out and nothing else is contracted: the same
+// bits in every kernel that evaluates a face.
 template <int NDIM, int AX, bool TWICE = false>
 __host__ __device__ __forceinline__ void roe_flux(const double* qL, const double* qR, double gm1, double* F) {
+#pragma clang fp contract(off)
     constexpr int IE = NDIM + 1;
-    // left / right primitive states; rho^(-1/2) gives both sqrt(rho) and 1/rho
     const double rL = qL[0], rR = qR[0];
-    const double rsL = rsqrt_nr(rL), rsR = rsqrt_nr(rR);
-    const double irL = rsL * rsL, irR = rsR * rsR;
+    const double rr = sign_from(rL * rR, rL);
+    const double y = rsqrt_nr(rr);
+    const double y2 = y * y;
+    const double irL = rR * y2, irR = rL * y2;
+    const double rt = rr * y;
+    const double wR = rR * rcp_nr(rR + rt);
+    // velocities, pressures, total enthalpies
     double uL[NDIM], uR[NDIM];
-    double qqL = 0.0, qqR = 0.0;
 #pragma unroll
     for (int d = 0; d < NDIM; ++d) {
         uL[d] = qL[1 + d] * irL;
         uR[d] = qR[1 + d] * irR;
-        qqL += uL[d] * uL[d];
-        qqR += uR[d] * uR[d];
     }
-    const double pL = gm1 * (qL[IE] - 0.5 * rL * qqL);
-    const double pR = gm1 * (qR[IE] - 0.5 * rR * qqR);
-    const double HL = (qL[IE] + pL) * irL;
-    const double HR = (qR[IE] + pR) * irR;
-    const double vnL = uL[AX], vnR = uR[AX];
-
-    // Roe averages with weights sqrt(rho) / (sqrt(rhoL) + sqrt(rhoR))
-    const double sL = rL * rsL, sR = rR * rsR;
-    const double iw = rcp_nr(sL + sR);
-    const double wL = sL * iw, wR = sR * iw;
-    double ut[NDIM];
-    double qqt = 0.0;
+    double keL = qL[1] * uL[0], keR = qR[1] * uR[0];
 #pragma unroll
-    for (int d = 0; d < NDIM; ++d) {
-        ut[d] = wL * uL[d] + wR * uR[d];
-        qqt += ut[d] * ut[d];
+    for (int d = 1; d < NDIM; ++d) {
+        keL = fma(qL[1 + d], uL[d], keL);
+        keR = fma(qR[1 + d], uR[d], keR);
     }
-    const double Ht = wL * HL + wR * HR;
-    const double rt = sL * sR;
-    const double c2 = gm1 * (Ht - 0.5 * qqt);
+    const double pL = gm1 * fma(-0.5, keL, qL[IE]);
+    const double pR = gm1 * fma(-0.5, keR, qR[IE]);
+    const double hL = qL[IE] + pL, hR = qR[IE] + pR;
+    const double HL = hL * irL, HR = hR * irR;
+    // Roe averages
+    double ut[NDIM];
+#pragma unroll
+    for (int d = 0; d < NDIM; ++d) ut[d] = fma(wR, uR[d] - uL[d], uL[d]);
+    double qqt = ut[0] * ut[0];
+#pragma unroll
+    for (int d = 1; d < NDIM; ++d) qqt = fma(ut[d], ut[d], qqt);
+    const double Ht = fma(wR, HR - HL, HL);
+    const double c2 = gm1 * fma(-0.5, qqt, Ht);
     const double rc = rsqrt_nr(c2);
     const double c = c2 * rc;
-    const double ic2 = rc * rc;
-    const double un = ut[AX];
-
-    // wave strengths
+    const double un = ut[AX], aun = fabs(un);
+    // acoustic part
+    const double m = fmin(fmax(aun * rc, 0.0), 1.0);
+    const double sm = copysign(m, un);
     const double dp = pR - pL;
-    const double dun = vnR - vnL;
-    const double rcdu = rt * c * dun;
-    const double hic2 = 0.5 * ic2;  // exact scaling: a1, a5 as (0.5 (dp -+ rcdu)) / c^2
-    const double a1 = (dp - rcdu) * hic2;
-    const double a2 = (rR - rL) - dp * ic2;
-    const double a5 = (dp + rcdu) * hic2;
-    // |lambda| times strength
-    const double w1 = fabs(un - c) * a1;
-    const double w2 = fabs(un) * a2;
-    const double w5 = fabs(un + c) * a5;
-    const double aun = fabs(un) * rt;  // |u_n| rho~ (shear waves)
-
-    // dissipation D = sum_k |lambda_k| alpha_k r_k
-    double D[NDIM + 2];
-    const double w15 = w1 + w5;
-    D[0] = w15 + w2;
-#pragma unroll
-    for (int d = 0; d < NDIM; ++d) {
-        if (d == AX)
-            D[1 + d] = w15 * ut[d] + (w5 - w1) * c + w2 * ut[d];
-        else
-            D[1 + d] = (w15 + w2) * ut[d] + aun * (uR[d] - uL[d]);
-    }
-    double De = w15 * Ht + (w5 - w1) * un * c + w2 * 0.5 * qqt;
-#pragma unroll
-    for (int d = 0; d < NDIM; ++d)
-        if (d != AX) De += aun * (uR[d] - uL[d]) * ut[d];
-    D[IE] = De;
-
-    // central part: physical fluxes of both sides (the mass flux rho u_n is
-    // the normal momentum itself)
+    const double rdu = rt * (uR[AX] - uL[AX]);
+    const double A = fma(fma(-rc, m, rc), dp, sm * rdu);
+    const double B = fma(sm, dp, fma(-c, m, c) * rdu);
+    // fluxes of both sides (the mass flux rho u_n is the normal momentum itself) minus the dissipation
     const double mL = qL[1 + AX], mR = qR[1 + AX];
     constexpr double h = TWICE ? 1.0 : 0.5;
-    F[0] = h * (mL + mR - D[0]);
+    F[0] = h * (fma(-aun, rR - rL, mL + mR) - A);
 #pragma unroll
     for (int d = 0; d < NDIM; ++d) {
-        double fl = mL * uL[d], fr = mR * uR[d];
-        if (d == AX) {
-            fl += pL;
-            fr += pR;
-        }
-        F[1 + d] = h * (fl + fr - D[1 + d]);
+        double f = d == AX ? fma(mR, uR[d], fma(mL, uL[d], pL + pR)) : fma(mR, uR[d], mL * uL[d]);
+        f = fma(-A, ut[d], fma(-aun, qR[1 + d] - qL[1 + d], f));
+        F[1 + d] = h * (d == AX ? f - B : f);
     }
-    F[IE] = h * ((qL[IE] + pL) * vnL + (qR[IE] + pR) * vnR - D[IE]);
+    F[IE] = h * fma(-B, un, fma(-A, Ht, fma(-aun, qR[IE] - qL[IE], fma(hR, uR[AX], hL * uL[AX]))));
 }
 
 // Roe flux through a 2D face of unit normal (nx, ny), conserved face states

@@ -139,7 +139,6 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
     // into the grid (lanes outside feed no output)
     Rsrc rmx, rmy, rmc;
     uint32_t sfx = 0, sfy = 0, scl = 0, xfo = 0, cfo = 0, xwo = 0;
-    double wyn[2][2];  // unit normals of the y faces at this lane's column on the low and high y boundary
     if (CURV) {
         const MetricOffsets mo = metric_offsets(G.nx, G.ny);
         rmx = grid_rsrc(met + mo.fx, 3 * mo.nfx * 8);
@@ -151,12 +150,6 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
         xfo = (uint32_t)(col < 0 ? 0 : (col > G.nx ? G.nx : col)) * 8u;
         cfo = (uint32_t)(col < 0 ? 0 : (col > G.nx - 1 ? G.nx - 1 : col)) * 8u;
         xwo = (uint32_t)(xside ? G.nx : 0) * 8u;  // the x wall face of this lane's side
-#pragma unroll
-        for (int sd = 0; sd < 2; ++sd) {
-            const uint32_t yo = (uint32_t)((long long)(sd ? G.ny : 0) * G.nx * 8);
-            wyn[sd][0] = ld_buf(rmy, cfo, yo);
-            wyn[sd][1] = ld_buf(rmy, cfo, sfy + yo);
-        }
     }
     // byte offsets of the metric rows: x faces and cells of row r, y faces of face row r (0 .. ny)
     auto mx_row = [&](int r) {
@@ -180,9 +173,11 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
         const int ys = r < 0 ? 0 : 1;
         if (CURV) {
             // a slip wall's mirror cell has its velocity reflected about the
-            // wall face's unit normal n: m - 2 (m . n) n
+            // wall face's unit normal n: m - 2 (m . n) n (the y wall's read here,
+            // by the few rows behind it: kept, it took 8 registers)
             if (yk == 2) {
-                const double nx = ys ? wyn[1][0] : wyn[0][0], ny = ys ? wyn[1][1] : wyn[0][1];
+                const uint32_t yo = (uint32_t)((long long)(ys ? G.ny : 0) * G.nx * 8);
+                const double nx = ld_buf(rmy, cfo, yo), ny = ld_buf(rmy, cfo, sfy + yo);
                 const double mn = w[1] * nx + w[2] * ny;
                 w[1] -= 2.0 * mn * nx;
                 w[2] -= 2.0 * mn * ny;

@@ -679,7 +679,10 @@ static void launch_flux_t(const double* U, double* F, const Geo& g, int bx, int 
         if (gy > 65535) gy = 65535;  // rows_j <= 65535 * by for every valid grid
         grid = dim3(blocks_for(cols, bx), gy, runs);
     }
-#define FV_LFR(T) hipLaunchKernelGGL((k_flux_run<NDIM, (AX > 0 ? AX : 1), T, FLUX_RUN>), grid, block, 0, s, U, F, g)
+    // (3D runs have at most 512 threads, see above: no kernel is built for 1024)
+#define FV_LFR(T) \
+    hipLaunchKernelGGL((k_flux_run<NDIM, (AX > 0 ? AX : 1), (NDIM == 3 && T > 512 ? 512 : T), FLUX_RUN>), grid, block, 0, \
+                       s, U, F, g)
     FV_DISPATCH_THREADS(threads, FV_LFR)
 #undef FV_LFR
 }
