@@ -278,7 +278,11 @@ int fv_clear_status(fv_ctx* ctx);
  * same result. Both paths compute the same cell arithmetic; fv_residual always
  * uses the split kernels, and fv_adjoint_step recomputes its stage states with
  * the fused stage kernels of the current table (the library's choice until a
- * table is set) on every grid the fused path takes. Returns FV_ENOTSUP for states
+ * table is set) on every grid the fused path takes. Small 2D grids (at most
+ * two 16 x 16-cell tiles per compute unit) take a whole step in one launch
+ * while the stage table is at the library's choice, with the same bits as the
+ * stage kernels; an odd number of steps then adds a copy of the state from
+ * the workspace. Returns FV_ENOTSUP for states
  * of 4 GiB or more (the fused kernels address a grid through 32-bit buffer
  * offsets) and for 3D viscous grids, and FV_EINVAL for other seg values. The
  * fused path takes every boundary kind and curvilinear 2D grids. */
@@ -318,7 +322,8 @@ int fv_get_path(const fv_ctx* ctx, int32_t* path, int32_t* seg, int32_t* waves);
  * fv_adjoint_step is bracketed by two HIP events on the context's stream and
  * each call waits for its last event, so enabling it serialises the host with
  * the stream; kernel durations themselves are unaffected. fv_get_timing
- * writes, per timer (FV_SITE_* and FV_TIMER_FUSED for the fused stages), the
+ * writes, per timer (FV_SITE_* and FV_TIMER_FUSED for the fused stages, or
+ * the whole steps of small grids), the
  * accumulated milliseconds and number of launches since the last read, then
  * resets them. Either output may be NULL. */
 enum { FV_TIMER_FUSED = 7, FV_NTIMERS = 8 };

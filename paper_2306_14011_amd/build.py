@@ -33,7 +33,8 @@ HIP_FLAGS = [
 # item is computed before the plane or row loop and the others inside it:
 # every segment height must give the same bits.
 FILE_FLAGS = {"fv_kernels.hip": ["-ffp-contract=on"], "fv_fused3d.hip": ["-ffp-contract=on"],
-              "fv_fused_curv.hip": ["-ffp-contract=on"], "fv_fused.hip": ["-ffp-contract=on"]}
+              "fv_fused_curv.hip": ["-ffp-contract=on"], "fv_fused.hip": ["-ffp-contract=on"],
+              "fv_step2d.hip": ["-ffp-contract=on"]}
 
 
 def sources():

@@ -31,6 +31,10 @@ struct fv_ctx {
     // fused path
     int path, fseg[3], fwaves[3], fitems[3];   // per Runge-Kutta stage
     int finit;             // work items of the 3D initial wave-speed kernel
+    int fauto[3];          // the library's segment heights
+    fvk::FGrid hgrid;      // the 2D grid's description (host copy)
+    double* sws;           // scratch of the whole-step kernel
+    int cus;               // compute units of the device
     fvk::FGrid* fgrid[3];  // the fused path's grid description per stage (an FGrid3 in 3D); they differ in seg
     unsigned long long* flam;
     double* fdt;
@@ -67,7 +71,7 @@ struct Layout {
     int64_t faces[3];
     int64_t ncell;
     int max_partial;
-    size_t off_status, off_dt, off_fused, off_lam, off_partial, off_U1, off_U2, off_F[3], off_R, off_lamA, off_lamB, off_met,
+    size_t off_status, off_dt, off_fused, off_lam, off_step, off_partial, off_U1, off_U2, off_F[3], off_R, off_lamA, off_lamB, off_met,
         total;
 };
 
@@ -171,6 +175,8 @@ int validate(const fv_grid_desc* g, Layout* L, char* why) {
     o += 2048;
     L->off_lam = o;
     o = align256(o + fvk::lam_bytes(1));
+    L->off_step = o;
+    if (nd == 2) o = align256(o + fvk::step2d_bytes());
     L->off_partial = o;
     o = align256(o + (size_t)L->max_partial * 8);
     const size_t state = (size_t)L->nvar * L->sv * 8;
@@ -418,6 +424,7 @@ int fv_create(const fv_grid_desc* g, void* workspace, size_t workspace_bytes, vo
         delete c;
         return fail(nullptr, FV_EDEVICE, "hipGetDevice failed%s");
     }
+    if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) c->cus = 0;
     char* base = (char*)workspace;
     c->status = (uint32_t*)(base + L.off_status);
     c->dt = (double*)(base + L.off_dt);
@@ -432,6 +439,7 @@ int fv_create(const fv_grid_desc* g, void* workspace, size_t workspace_bytes, vo
     for (int st = 0; st < 3; ++st) c->fgrid[st] = (fvk::FGrid*)(base + L.off_fused + 512 * st);
     c->flam = (unsigned long long*)(base + L.off_lam);
     c->fdt = (double*)(base + L.off_fused + 1536);
+    c->sws = (double*)(base + L.off_step);
     c->path = FV_PATH_SPLIT;
     if (g->nodes) {
         double* met = (double*)(base + L.off_met);
@@ -527,9 +535,45 @@ static int fused_step3(fv_ctx* c, double* U, int32_t nsteps, const double* dt_in
     return FV_OK;
 }
 
+// Whether a fused step of this grid runs as one launch (fv_step2d.hip): small
+// 2D grids (step2d_pays) with the stage table at the library's choice
+// (another table asks for the stage kernels, cut as it says). On a
+// curvilinear grid the two end faces of a periodic axis are computed from
+// different nodes and may differ in the last bit, so a tile's copy of a cell
+// beyond the end would not have the cell's bits: those grids keep the stage
+// kernels.
+static bool whole_step(const fv_ctx* c) {
+    if (c->g.ndim != 2 || !fvk::step2d_pays(c->hgrid, c->cus)) return false;
+    if (c->g.met && (c->g.bc[0][0] == FV_BC_PERIODIC || c->g.bc[1][0] == FV_BC_PERIODIC)) return false;
+    for (int st = 0; st < 3; ++st)
+        if (c->fwaves[st] != 0 || c->fseg[st] != c->fauto[st]) return false;
+    return true;
+}
+
+static int whole_steps(fv_ctx* c, double* U, int32_t nsteps, const double* dt_in, double* dt_out) {
+    const int mode = c->g.met ? 3 : (c->g.mu > 0.0 ? 2 : (has_walls(c) ? 1 : 0));
+    const double* gq = &c->fgrid[0]->q[0][0][0];
+    if (!dt_in) fvk::launch_step2d_init(c->hgrid, U, c->sws, c->status, c->g.met, c->stream);
+    for (int32_t s = 0; s < nsteps; ++s) {
+        {
+            SiteTimer t(c, FV_TIMER_FUSED);
+            fvk::launch_step2d(c->hgrid, c->cus, gq, s & 1 ? c->U1 : U, s & 1 ? U : c->U1, c->sws, s,
+                               dt_in ? dt_in + s : nullptr, c->fdt, dt_out ? dt_out + s : nullptr, c->status, c->src,
+                               mode, c->g.met, c->stream);
+        }
+        int rc = check_launch_error(c);
+        if (rc != FV_OK) return rc;
+        rc = drain_timing(c);
+        if (rc != FV_OK) return rc;
+    }
+    if (nsteps & 1) fvk::launch_step2d_copy(c->hgrid, c->U1, U, c->stream);
+    return check_launch_error(c);
+}
+
 static int fused_step(fv_ctx* c, double* U, int32_t nsteps, const double* dt_in, double* dt_out) {
     if (nsteps == 0) return FV_OK;
     if (c->g.ndim == 3) return fused_step3(c, U, nsteps, dt_in, dt_out);
+    if (whole_step(c)) return whole_steps(c, U, nsteps, dt_in, dt_out);
     const int walls = c->g.met ? 3 : (c->g.mu > 0.0 ? 2 : (has_walls(c) ? 1 : 0));
     unsigned long long* first = fvk::lam_first(c->flam, 1);
     fvk::launch_fused_init(c->fgrid[0], 1, c->fitems[0], U, first, c->status, c->stream, c->g.met);
@@ -592,7 +636,8 @@ static int set_fused_stage(fv_ctx* c, int st, int32_t seg, int32_t waves) {
         G.gamma = c->g.gamma;
         G.gm1 = c->g.gm1;
         memcpy(G.q, c->bcs.q, sizeof(G.q));
-        if (seg == 0) seg = fvk::fused3d_auto_seg(G, fvk::fused3d_slots());
+        c->fauto[st] = fvk::fused3d_auto_seg(G, fvk::fused3d_slots());
+        if (seg == 0) seg = c->fauto[st];
         G.seg = seg;
         e = hipMemcpyAsync(c->fgrid[st], &G, sizeof(G), hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -627,8 +672,10 @@ static int set_fused_stage(fv_ctx* c, int st, int32_t seg, int32_t waves) {
         G.mu = c->g.mu;
         G.kcond = c->g.kcond;
         G.nu_fac = c->g.nu_fac;
-        if (seg == 0) seg = fvk::fused_auto_seg(&G, 1, fvk::fused_slots());
+        c->fauto[st] = fvk::fused_auto_seg(&G, 1, fvk::fused_slots());
+        if (seg == 0) seg = c->fauto[st];
         G.seg = seg;
+        c->hgrid = G;
         e = hipMemcpyAsync(c->fgrid[st], &G, sizeof(G), hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         c->fitems[st] = fvk::fused_items(G, seg);

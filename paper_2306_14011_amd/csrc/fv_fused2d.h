@@ -333,8 +333,8 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
         roe_flux<2, 1, true>(qL, qR, G.gm1, Fy[0]);
     }
     // viscous variant: w = (u, v, T) of row r in Wv[(r - r0 + 2) & 3], like the
-    // window; the viscous y-face fluxes of face f in Vy[f & 1]
-    double Wv[4][3], Vy[2][3];
+    // window. The viscous flux is taken off the inviscid one (twice, like it)
+    double Wv[4][3];
     const double qdx = 0.25 * G.inv_dx, qdy = 0.25 * G.inv_dy;
     if (VISC) {
 #pragma clang fp contract(on)
@@ -345,7 +345,10 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
         for (int m = 0; m < 3; ++m)
             dt[m] = ((lane_shift1<false>(Wv[1][m]) - lane_shift1<true>(Wv[1][m])) +
                      (lane_shift1<false>(Wv[2][m]) - lane_shift1<true>(Wv[2][m]))) * qdx;
-        visc_flux2<1>(Wv[1], Wv[2], dt, G.inv_dy, G.mu, G.kcond, Vy[0]);
+        double V[3];
+        visc_flux2<1>(Wv[1], Wv[2], dt, G.inv_dy, G.mu, G.kcond, V);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) Fy[0][1 + m] = fma(-2.0, V[m], Fy[0][1 + m]);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll 1
@@ -415,7 +418,10 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
                     dt[m] = ((lane_shift1<false>(Wv[(t + 1) & 3][m]) - wl0[m]) +
                              (lane_shift1<false>(Wv[(t + 2) & 3][m]) - wl1[m])) * qdx;
                 }
-                visc_flux2<1>(Wv[(t + 1) & 3], Wv[(t + 2) & 3], dt, G.inv_dy, G.mu, G.kcond, Vy[t & 1]);
+                double V[3];
+                visc_flux2<1>(Wv[(t + 1) & 3], Wv[(t + 2) & 3], dt, G.inv_dy, G.mu, G.kcond, V);
+#pragma unroll
+                for (int m = 0; m < 3; ++m) Fy[t & 1][1 + m] = fma(-2.0, V[m], Fy[t & 1][1 + m]);
             }
             // x faces of row rr: this lane computes its left face; its right
             // face is the left face of the lane above. Each lane forms its
@@ -442,11 +448,8 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
             } else {
                 roe_flux<2, 0, true>(qL, qR, G.gm1, Fxl);
             }
-#pragma unroll
-            for (int v = 0; v < NV; ++v) Fxr[v] = lane_shift1<false>(Fxl[v]);
             // viscous x face left of this lane (columns i - 1 and i of row
             // rr), tangential derivative from rows rr - 1 and rr + 1
-            double Vxl[3], Vxr[3];
             if (VISC) {
 #pragma clang fp contract(on)
                 double dt[3];
@@ -455,10 +458,13 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
                     const double lo_m = lane_shift1<true>(Wv[t][m]);  // (i - 1, rr - 1)
                     dt[m] = ((wl1[m] - lo_m) + (Wv[(t + 2) & 3][m] - Wv[t][m])) * qdy;
                 }
-                visc_flux2<0>(wl0, Wv[(t + 1) & 3], dt, G.inv_dx, G.mu, G.kcond, Vxl);
+                double V[3];
+                visc_flux2<0>(wl0, Wv[(t + 1) & 3], dt, G.inv_dx, G.mu, G.kcond, V);
 #pragma unroll
-                for (int m = 0; m < 3; ++m) Vxr[m] = lane_shift1<false>(Vxl[m]);
+                for (int m = 0; m < 3; ++m) Fxl[1 + m] = fma(-2.0, V[m], Fxl[1 + m]);
             }
+#pragma unroll
+            for (int v = 0; v < NV; ++v) Fxr[v] = lane_shift1<false>(Fxl[v]);
             const bool row_ok = rr < G.ny;  // uniform
             const uint32_t p = out_row(rr);
             const uint32_t so = row_ok ? sboff : DROP_OFFSET;
@@ -477,11 +483,6 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
                 double r = CURV ? Fxr[v] - Fxl[v] : (Fxr[v] - Fxl[v]) * hax;
                 if (CURV) r += Fy[t & 1][v] - Fy[(t + 1) & 1][v];
                 else r += (Fy[t & 1][v] - Fy[(t + 1) & 1][v]) * hay;
-                if (VISC && v > 0) {
-                    // minus the viscous face fluxes (Eq. (residual): F_i,n - F_nu,n)
-                    r -= (Vxr[v - 1] - Vxl[v - 1]) * G.ax;
-                    r -= (Vy[t & 1][v - 1] - Vy[(t + 1) & 1][v - 1]) * G.ay;
-                }
                 if (SRC) r -= (CURV ? Ma[t & 1] : vol) * Sv[v];  // R = flux sum - |Omega| S
                 if (STAGE == 0) {
                     out[v] = c[v] + sc * r;

@@ -101,6 +101,18 @@ int fused3d_init_items(const FGrid3& G);
 int fused3d_auto_seg(const FGrid3& G, int slots);
 int fused_auto_seg(const FGrid* grids, int ngrids, int slots);
 
+// whole 2D steps in one launch each (fv_step2d.hip); cus: the device's compute units. ws: step2d_bytes() of
+// scratch; step: the step's number in the call; launch_step2d_init: the first
+// step's wave speeds (with dt_in null)
+size_t step2d_bytes();
+void launch_step2d_init(const FGrid& G, const double* U, double* ws, uint32_t* status, const double* met,
+                        hipStream_t s);
+bool step2d_pays(const FGrid& G, int cus);
+void launch_step2d(const FGrid& G, int cus, const double* gq, const double* Un, double* Ud, double* ws, int step,
+                   const double* dt_in, double* dtg, double* dt_out, uint32_t* status, const double* src, int mode,
+                   const double* met, hipStream_t s);
+void launch_step2d_copy(const FGrid& G, const double* from, double* to, hipStream_t s);
+
 // adjoint: one reverse Runge-Kutta stage (mode 3, 2, 1 for stages 3, 2, 1)
 void launch_adj_stage(int mode, const double* Us, const double* w, double* lam, double* lamA, double* lamB, double* R,
                       const double* dt, const Geo& g, const BcState& bcs, hipStream_t s);
