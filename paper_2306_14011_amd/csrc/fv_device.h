@@ -372,307 +372,186 @@ __host__ __device__ __forceinline__ double curv_cell_lambda(const double* q, dou
 
 // ---------------------------------------------------------------------------
 // Reverse (adjoint) of the face computation, hand-derived from the forward
-// sequence above: given Fb = dJ/dF, accumulate dJ/dq of the four stencil
-// cells. Branches (minmod selection, |lambda| signs) follow the forward
-// evaluation; |x| has derivative 0 at x = 0.
+// sequence above. The selections of a limiter follow the forward evaluation;
+// |x| has derivative 0 at x = 0. The rule LIM is fixed at compile time (0
+// minmod, 1 Psi = 1 with kappa = -1, 2 the kappa weights ka, kb, 3 van Leer)
+// and the selections are selects: with the scheme tested at run time and the
+// limiter's cases as branches, a face took some 700 basic blocks.
 
-// MUSCL-minmod reverse for one variable: qLb = dJ/dQL, qRb = dJ/dQR.
-// g0..g3 receive dJ/dq of cells k-1, k, k+1, k+2 (accumulated).
-__host__ __device__ __forceinline__ void muscl_minmod_vjp(double q0, double q1, double q2, double q3, double qLb,
-                                                          double qRb, double& g0, double& g1, double& g2,
-                                                          double& g3) {
-    const double dm = q1 - q0, dc = q2 - q1, dp = q3 - q2;
-    // QL = q1 + minmod(dm, dc) / 2 (Psi(dc/dm) dm: the dm branch at a tie)
-    if (((dm > 0.0) & (dc > 0.0)) | ((dm < 0.0) & (dc < 0.0))) {
-        if (fabs(dm) <= fabs(dc)) {  // q1 + (q1 - q0)/2
-            g1 += 1.5 * qLb;
-            g0 -= 0.5 * qLb;
-        } else {  // (q1 + q2)/2
-            g1 += 0.5 * qLb;
-            g2 += 0.5 * qLb;
+// Face states of one variable, with what their reverse needs: the stencil's
+// differences and the two limited slopes (mL of the left cell, mR of the right).
+template <int LIM>
+struct FaceVar {
+    double dm, dc, dp, mL, mR;
+    __host__ __device__ __forceinline__ void states(const double* q, double ka, double kb, double& qL, double& qR) {
+        dm = q[1] - q[0];
+        dc = q[2] - q[1];
+        dp = q[3] - q[2];
+        if (LIM == 2) {
+            muscl_kappa_diffs(q[1], q[2], dm, dc, dp, ka, kb, qL, qR);
+            mL = mR = 0.0;
+        } else {
+            mL = LIM == 1 ? dm : (LIM == 3 ? vanleer(dm, dc) : minmod(dm, dc));
+            mR = LIM == 1 ? dp : (LIM == 3 ? vanleer(dc, dp) : minmod(dp, dc));
+            qL = q[1] + 0.5 * mL;
+            qR = q[2] - 0.5 * mR;
         }
-    } else {
-        g1 += qLb;
     }
-    // QR = q2 - minmod(dp, dc) / 2; at a tie |dp| = |dc| both branches give the
-    // same value, and the derivative follows the limiter written as
-    // Psi(dp/dc) dc with Psi saturating at ratio >= 1, i.e. the dc branch
-    if (((dp > 0.0) & (dc > 0.0)) | ((dp < 0.0) & (dc < 0.0))) {
-        if (fabs(dp) < fabs(dc)) {  // 3/2 q2 - q3/2
-            g2 += 1.5 * qRb;
-            g3 -= 0.5 * qRb;
-        } else {  // (q1 + q2)/2
-            g1 += 0.5 * qRb;
-            g2 += 0.5 * qRb;
+    // g[0..3]: dJ/dq of the stencil from qLb = dJ/dQ^L, qRb = dJ/dQ^R.
+    __host__ __device__ __forceinline__ void reverse(double qLb, double qRb, double ka, double kb, double* g) const {
+        const double hl = 0.5 * qLb, hr = 0.5 * qRb;
+        double am, ac, ap;  // dJ/d of the three differences
+        if (LIM == 1) {
+            am = hl;
+            ac = 0.0;
+            ap = -hr;
+        } else if (LIM == 2) {
+            am = ka * qLb;
+            ac = kb * (qLb - qRb);
+            ap = -ka * qRb;
+        } else if (LIM == 3) {
+            // d vl(a, b)/da = 2 b^2 / (a + b)^2 and symmetric, zero unless a and b share a sign
+            const double sl = dm + dc, sr = dc + dp;
+            const bool l = mL != 0.0, r = mR != 0.0;
+            const double il = l ? 2.0 / (sl * sl) : 0.0, ir = r ? 2.0 / (sr * sr) : 0.0;
+            am = il * dc * dc * hl;
+            ac = il * dm * dm * hl - ir * dp * dp * hr;
+            ap = -ir * dc * dc * hr;
+        } else {
+            // the limited slope is one of its two differences or zero; at a tie the
+            // derivative follows the limiter as Psi(ratio) x difference, saturating
+            // at ratio >= 1: dm for the left state, dc for the right
+            const bool ml = mL != 0.0, mr = mR != 0.0;
+            const bool lm = mL == dm, rc = mR == dc;
+            am = ml && lm ? hl : 0.0;
+            ac = (ml && !lm ? hl : 0.0) - (mr && rc ? hr : 0.0);
+            ap = mr && !rc ? -hr : 0.0;
         }
-    } else {
-        g2 += qRb;
+        g[0] = -am;
+        g[1] = qLb + (am - ac);
+        g[2] = qRb + (ac - ap);
+        g[3] = ap;
     }
-}
-
-// Reverse of muscl(): the unlimited states are linear in the stencil,
-// Q^L = (1 - b + a) q1 - a q0 + b q2 and Q^R = (1 - b + a) q2 + b q1 - a q3
-// (a = 1/2, b = 0 for kappa = -1).
-__host__ __device__ __forceinline__ void muscl_vjp(double q0, double q1, double q2, double q3, int scheme,
-                                                   double qLb, double qRb, double& g0, double& g1, double& g2,
-                                                   double& g3) {
-    if (scheme == 1) {
-        g1 += 1.5 * qLb;
-        g0 -= 0.5 * qLb;
-        g2 += 1.5 * qRb;
-        g3 -= 0.5 * qRb;
-    } else if (scheme == 0) {
-        muscl_minmod_vjp(q0, q1, q2, q3, qLb, qRb, g0, g1, g2, g3);
-    } else if (scheme == 5) {
-        // d vl(a, b)/da = 2 b^2 / (a + b)^2 and symmetric, zero unless ab > 0
-        const double dm = q1 - q0, dc = q2 - q1, dp = q3 - q2;
-        double ga = 0.0, gb = 0.0, ha = 0.0, hb = 0.0;
-        if (dm * dc > 0.0) {
-            const double i2 = 2.0 / ((dm + dc) * (dm + dc));
-            ga = i2 * dc * dc;
-            gb = i2 * dm * dm;
-        }
-        if (dc * dp > 0.0) {
-            const double i2 = 2.0 / ((dc + dp) * (dc + dp));
-            ha = i2 * dp * dp;
-            hb = i2 * dc * dc;
-        }
-        g0 -= 0.5 * ga * qLb;
-        g1 += (1.0 + 0.5 * ga - 0.5 * gb) * qLb + 0.5 * ha * qRb;
-        g2 += 0.5 * gb * qLb + (1.0 - 0.5 * ha + 0.5 * hb) * qRb;
-        g3 -= 0.5 * hb * qRb;
-    } else {
-        double a, b;
-        kappa_weights(scheme, a, b);
-        const double c = 1.0 - b + a;
-        g0 -= a * qLb;
-        g1 += c * qLb + b * qRb;
-        g2 += b * qLb + c * qRb;
-        g3 -= a * qRb;
-    }
-}
+};
 
 __host__ __device__ __forceinline__ double sgn0(double x) { return x > 0.0 ? 1.0 : (x < 0.0 ? -1.0 : 0.0); }
 
-// Reverse of roe_flux<NDIM, AX>: Fb[NV] in, qLb[NV] and qRb[NV] out (overwritten).
+// Reverse of roe_flux<NDIM, AX>: Fb[NV] in, qLb[NV] and qRb[NV] out
+// (overwritten). The forward quantities are evaluated as there (the flux
+// itself is not needed).
 template <int NDIM, int AX>
 __host__ __device__ __forceinline__ void roe_flux_vjp(const double* qL, const double* qR, double gm1, const double* Fb,
                                                       double* qLb, double* qRb) {
     constexpr int IE = NDIM + 1;
-    // ---- forward recomputation (as in roe_flux) ----
     const double rL = qL[0], rR = qR[0];
-    const double rsL = rsqrt_nr(rL), rsR = rsqrt_nr(rR);
-    const double irL = rsL * rsL, irR = rsR * rsR;
-    double uL[NDIM], uR[NDIM];
-    double qqL = 0.0, qqR = 0.0;
+    const double rr = sign_from(rL * rR, rL);
+    const double y = rsqrt_nr(rr);
+    const double y2 = y * y;
+    const double irL = rR * y2, irR = rL * y2;
+    const double rt = rr * y;
+    const double wR = rR * rcp_nr(rR + rt);
+    double uL[NDIM], uR[NDIM], du[NDIM], ut[NDIM];
+    double keL = 0.0, keR = 0.0, qqt = 0.0;
+#pragma unroll
     for (int d = 0; d < NDIM; ++d) {
         uL[d] = qL[1 + d] * irL;
         uR[d] = qR[1 + d] * irR;
-        qqL += uL[d] * uL[d];
-        qqR += uR[d] * uR[d];
-    }
-    const double EL = qL[IE], ER = qR[IE];
-    const double pL = gm1 * (EL - 0.5 * rL * qqL);
-    const double pR = gm1 * (ER - 0.5 * rR * qqR);
-    const double HL = (EL + pL) * irL;
-    const double HR = (ER + pR) * irR;
-    const double vnL = uL[AX], vnR = uR[AX];
-    const double sL = rL * rsL, sR = rR * rsR;
-    const double iw = rcp_nr(sL + sR);
-    const double wL = sL * iw, wR = sR * iw;
-    double ut[NDIM];
-    double qqt = 0.0;
-    for (int d = 0; d < NDIM; ++d) {
-        ut[d] = wL * uL[d] + wR * uR[d];
+        keL += qL[1 + d] * uL[d];
+        keR += qR[1 + d] * uR[d];
+        du[d] = uR[d] - uL[d];
+        ut[d] = uL[d] + wR * du[d];
         qqt += ut[d] * ut[d];
     }
-    const double Ht = wL * HL + wR * HR;
-    const double rt = sL * sR;
+    const double pL = gm1 * (qL[IE] - 0.5 * keL), pR = gm1 * (qR[IE] - 0.5 * keR);
+    const double hL = qL[IE] + pL, hR = qR[IE] + pR;
+    const double HL = hL * irL, dH = hR * irR - HL;
+    const double Ht = HL + wR * dH;
     const double c2 = gm1 * (Ht - 0.5 * qqt);
-    const double rc = rsqrt_nr(c2);
-    const double c = c2 * rc;
-    const double ic2 = rc * rc;
-    const double un = ut[AX];
+    const double rc = rsqrt_nr(c2), c = c2 * rc;
+    const double un = ut[AX], aun = fabs(un);
+    const bool sub = aun * rc < 1.0;  // subsonic: the acoustic speeds' branch
+    const double m = sub ? aun * rc : 1.0, om = 1.0 - m;
+    const double sm = copysign(m, un);
     const double dp = pR - pL;
-    const double dun = vnR - vnL;
-    const double rcdu = rt * c * dun;
-    const double hic2 = 0.5 * ic2;  // exact scaling: a1, a5 as (0.5 (dp -+ rcdu)) / c^2
-    const double a1 = (dp - rcdu) * hic2;
-    const double a2 = (rR - rL) - dp * ic2;
-    const double a5 = (dp + rcdu) * hic2;
-    const double l1 = fabs(un - c), l2 = fabs(un), l5 = fabs(un + c);
-    const double w1 = l1 * a1, w2 = l2 * a2, w5 = l5 * a5;
-    const double aun = l2 * rt;
-    const double w15 = w1 + w5;
-    const double fmL = rL * vnL, fmR = rR * vnR;  // mass fluxes
-
-    // ---- reverse ----
-    double rLb = 0.0, rRb = 0.0, ELb = 0.0, ERb = 0.0, pLb = 0.0, pRb = 0.0;
-    double vnLb = 0.0, vnRb = 0.0, fmLb = 0.0, fmRb = 0.0;
-    double uLb[NDIM], uRb[NDIM], utb[NDIM];
-    for (int d = 0; d < NDIM; ++d) uLb[d] = uRb[d] = utb[d] = 0.0;
-    // F0 = (fmL + fmR - D0)/2; F[1+d] = (fmL uL + fmR uR + [d==AX](pL + pR) - D[1+d])/2;
-    // F[IE] = ((EL + pL) vnL + (ER + pR) vnR - De)/2
-    const double D0b = -0.5 * Fb[0];
-    fmLb += 0.5 * Fb[0];
-    fmRb += 0.5 * Fb[0];
-    double Db[NDIM];
+    const double rdu = rt * du[AX];
+    const double A = om * rc * dp + sm * rdu;
+    const double B = sm * dp + om * c * rdu;
+    // ---- reverse, f = Fb / 2 ----
+    const double f0 = 0.5 * Fb[0], fE = 0.5 * Fb[IE];
+    double f[NDIM], utb[NDIM], uLb[NDIM], uRb[NDIM];
+    double fuL = f0, fuR = f0, fut = f0;
+    double aunb = -(f0 * (rR - rL) + fE * (qR[IE] - qL[IE]));
+    const double mL = qL[1 + AX], mR = qR[1 + AX];
+#pragma unroll
     for (int d = 0; d < NDIM; ++d) {
-        const double f = 0.5 * Fb[1 + d];
-        fmLb += f * uL[d];
-        uLb[d] += f * fmL;
-        fmRb += f * uR[d];
-        uRb[d] += f * fmR;
-        if (d == AX) {
-            pLb += f;
-            pRb += f;
-        }
-        Db[d] = -f;
+        f[d] = 0.5 * Fb[1 + d];
+        fuL += f[d] * uL[d];
+        fuR += f[d] * uR[d];
+        fut += f[d] * ut[d];
+        aunb -= f[d] * (qR[1 + d] - qL[1 + d]);
+        utb[d] = -A * f[d];
+        uLb[d] = f[d] * mL;
+        uRb[d] = f[d] * mR;
     }
+    uLb[AX] += fE * hL;
+    uRb[AX] += fE * hR;
+    // acoustic part
+    const double Ab = -(fut + fE * Ht), Bb = -(f[AX] + fE * un);
+    const double smb = Ab * rdu + Bb * dp;
+    const double tib = Ab * dp, tb = Bb * rdu;
+    const double dpb = Ab * om * rc + Bb * sm;
+    const double rdub = Ab * sm + Bb * om * c;
+    const double omb = sub ? tib * rc + tb * c : 0.0, smu = sub ? smb : 0.0;
+    aunb -= omb * rc;
+    const double rcb = tib * om - omb * aun + smu * un;
+    const double c2b = 0.5 * rc * (tb * om - rcb * rc * rc);
+    utb[AX] += smu * rc - B * fE + aunb * sgn0(un);
+    const double gc = gm1 * c2b;
+    const double Htb = gc - A * fE;
+    uLb[AX] -= rdub * rt;
+    uRb[AX] += rdub * rt;
+    double wRb = Htb * dH;
+#pragma unroll
+    for (int d = 0; d < NDIM; ++d) {
+        const double b = utb[d] - gc * ut[d];
+        wRb += b * du[d];
+        const double br = wR * b;
+        uRb[d] += br;
+        uLb[d] += b - br;
+    }
+    const double HRb = wR * Htb, HLb = Htb - HRb;
+    // per side: h = E + p, H = h / rho, p = gm1 (E - m.u / 2), u = m / rho
+    const double rtw = rdub * du[AX] * rt, wwb = wRb * wR * (1.0 - wR);
     {
-        const double f = 0.5 * Fb[IE];
-        ELb += f * vnL;
-        pLb += f * vnL;
-        vnLb += f * (EL + pL);
-        ERb += f * vnR;
-        pRb += f * vnR;
-        vnRb += f * (ER + pR);
-    }
-    const double Deb = -0.5 * Fb[IE];
-    // mass fluxes fm = r vn
-    rLb += fmLb * vnL;
-    vnLb += fmLb * rL;
-    rRb += fmRb * vnR;
-    vnRb += fmRb * rR;
-    // De = w15 Ht + (w5 - w1) un c + w2 qqt/2 + sum_{d != AX} aun (uR - uL)_d ut_d
-    double w15b = 0.0, w1b = 0.0, w2b = 0.0, w5b = 0.0, Htb = 0.0, unb = 0.0, cb = 0.0, qqtb = 0.0, aunb = 0.0;
-    w15b += Deb * Ht;
-    Htb += Deb * w15;
-    w5b += Deb * un * c;
-    w1b -= Deb * un * c;
-    unb += Deb * (w5 - w1) * c;
-    cb += Deb * (w5 - w1) * un;
-    w2b += Deb * 0.5 * qqt;
-    qqtb += Deb * 0.5 * w2;
-    for (int d = 0; d < NDIM; ++d) {
-        if (d == AX) continue;
-        const double du = uR[d] - uL[d];
-        aunb += Deb * du * ut[d];
-        uRb[d] += Deb * aun * ut[d];
-        uLb[d] -= Deb * aun * ut[d];
-        utb[d] += Deb * aun * du;
-    }
-    // D[1+d]
-    for (int d = 0; d < NDIM; ++d) {
-        if (d == AX) {
-            // w15 ut + (w5 - w1) c + w2 ut
-            w15b += Db[d] * ut[d];
-            w2b += Db[d] * ut[d];
-            utb[d] += Db[d] * (w15 + w2);
-            w5b += Db[d] * c;
-            w1b -= Db[d] * c;
-            cb += Db[d] * (w5 - w1);
-        } else {
-            // (w15 + w2) ut + aun (uR - uL)
-            w15b += Db[d] * ut[d];
-            w2b += Db[d] * ut[d];
-            utb[d] += Db[d] * (w15 + w2);
-            aunb += Db[d] * (uR[d] - uL[d]);
-            uRb[d] += Db[d] * aun;
-            uLb[d] -= Db[d] * aun;
-        }
-    }
-    // D0 = w15 + w2
-    w15b += D0b;
-    w2b += D0b;
-    // w15 = w1 + w5
-    w1b += w15b;
-    w5b += w15b;
-    // aun = l2 rt; w_k = l_k a_k
-    double l1b = w1b * a1, l2b = w2b * a2 + aunb * rt, l5b = w5b * a5;
-    double rtb = aunb * l2;
-    const double a1b = w1b * l1, a2b = w2b * l2, a5b = w5b * l5;
-    // l1 = |un - c|, l2 = |un|, l5 = |un + c|
-    {
-        const double s1 = sgn0(un - c), s2 = sgn0(un), s5 = sgn0(un + c);
-        unb += l1b * s1 + l2b * s2 + l5b * s5;
-        cb += -l1b * s1 + l5b * s5;
-    }
-    // a5 = (dp + rcdu) ic2 / 2; a2 = dr - dp ic2; a1 = (dp - rcdu) ic2 / 2
-    double dpb = 0.5 * a5b * ic2 + 0.5 * a1b * ic2 - a2b * ic2;
-    const double rcdub = 0.5 * a5b * ic2 - 0.5 * a1b * ic2;
-    double ic2b = a5b * 0.5 * (dp + rcdu) + a1b * 0.5 * (dp - rcdu) - a2b * dp;
-    rRb += a2b;
-    rLb -= a2b;
-    // rcdu = rt c dun
-    rtb += rcdub * c * dun;
-    cb += rcdub * rt * dun;
-    const double dunb = rcdub * rt * c;
-    vnRb += dunb;
-    vnLb -= dunb;
-    pRb += dpb;
-    pLb -= dpb;
-    // ic2 = 1/c2; c = sqrt(c2); c2 = gm1 (Ht - qqt/2)
-    double c2b = -ic2b * ic2 * ic2 + cb * 0.5 * rc;
-    Htb += gm1 * c2b;
-    qqtb -= 0.5 * gm1 * c2b;
-    // rt = sL sR
-    double sLb = rtb * sR, sRb = rtb * sL;
-    // Ht = wL HL + wR HR
-    double wLb = Htb * HL, wRb = Htb * HR;
-    const double HLb = Htb * wL, HRb = Htb * wR;
-    // un is ut[AX]; qqt = sum ut^2; ut = wL uL + wR uR
-    utb[AX] += unb;
-    for (int d = 0; d < NDIM; ++d) {
-        utb[d] += 2.0 * ut[d] * qqtb;
-        wLb += utb[d] * uL[d];
-        uLb[d] += utb[d] * wL;
-        wRb += utb[d] * uR[d];
-        uRb[d] += utb[d] * wR;
-    }
-    // wL = sL iw, wR = sR iw, iw = 1/(sL + sR)
-    const double iwb = wLb * sL + wRb * sR;
-    sLb += wLb * iw;
-    sRb += wRb * iw;
-    const double sumb = -iwb * iw * iw;
-    sLb += sumb;
-    sRb += sumb;
-    rLb += sLb * 0.5 * rsL;
-    rRb += sRb * 0.5 * rsR;
-    // per side: H = (E + p) ir; p = gm1 (E - r qq / 2); qq = sum u^2; u = m ir; ir = 1/r
-    {
-        double irb = HLb * (EL + pL);
-        ELb += HLb * irL;
-        pLb += HLb * irL;
-        ELb += gm1 * pLb;
-        rLb -= 0.5 * gm1 * qqL * pLb;
-        const double qqb = -0.5 * gm1 * rL * pLb;
-        uLb[AX] += vnLb;
+        const double hb = fE * uL[AX] + HLb * irL;
+        const double pb = f[AX] - dpb + hb;
+        const double keb = -0.5 * gm1 * pb;
+        double irb = HLb * hL;
+        const double as = aun;
+#pragma unroll
         for (int d = 0; d < NDIM; ++d) {
-            uLb[d] += 2.0 * uL[d] * qqb;
-            qLb[1 + d] = uLb[d] * irL;
-            irb += uLb[d] * qL[1 + d];
+            const double ub = uLb[d] + keb * qL[1 + d];
+            irb += ub * qL[1 + d];
+            qLb[1 + d] = ub * irL + keb * uL[d] + as * f[d];
         }
-        rLb -= irb * irL * irL;
-        qLb[0] = rLb;
-        qLb[IE] = ELb;
+        qLb[1 + AX] += fuL;
+        qLb[IE] = hb + gm1 * pb + as * fE;
+        qLb[0] = irL * (0.5 * (rtw - wwb) - irb * irL) + as * f0;
     }
     {
-        double irb = HRb * (ER + pR);
-        ERb += HRb * irR;
-        pRb += HRb * irR;
-        ERb += gm1 * pRb;
-        rRb -= 0.5 * gm1 * qqR * pRb;
-        const double qqb = -0.5 * gm1 * rR * pRb;
-        uRb[AX] += vnRb;
+        const double hb = fE * uR[AX] + HRb * irR;
+        const double pb = f[AX] + dpb + hb;
+        const double keb = -0.5 * gm1 * pb;
+        double irb = HRb * hR;
+#pragma unroll
         for (int d = 0; d < NDIM; ++d) {
-            uRb[d] += 2.0 * uR[d] * qqb;
-            qRb[1 + d] = uRb[d] * irR;
-            irb += uRb[d] * qR[1 + d];
+            const double ub = uRb[d] + keb * qR[1 + d];
+            irb += ub * qR[1 + d];
+            qRb[1 + d] = ub * irR + keb * uR[d] - aun * f[d];
         }
-        rRb -= irb * irR * irR;
-        qRb[0] = rRb;
-        qRb[IE] = ERb;
+        qRb[1 + AX] += fuR;
+        qRb[IE] = hb + gm1 * pb - aun * fE;
+        qRb[0] = irR * (0.5 * (rtw + wwb) - irb * irR) - aun * f0;
     }
 }
 
