@@ -636,7 +636,7 @@ static int set_fused_stage(fv_ctx* c, int st, int32_t seg, int32_t waves) {
         G.gamma = c->g.gamma;
         G.gm1 = c->g.gm1;
         memcpy(G.q, c->bcs.q, sizeof(G.q));
-        c->fauto[st] = fvk::fused3d_auto_seg(G, fvk::fused3d_slots());
+        c->fauto[st] = fvk::fused3d_auto_seg(G, c->cus);
         if (seg == 0) seg = c->fauto[st];
         G.seg = seg;
         e = hipMemcpyAsync(c->fgrid[st], &G, sizeof(G), hipMemcpyHostToDevice, c->stream);

@@ -6,20 +6,28 @@
 // Work decomposition: a work item is a tile of TX x TY (32 x 7) cells of the (x, y)
 // plane over a segment of seg planes along z (seg a multiple of 4), and one
 // workgroup of 256 threads (four wavefronts) owns an item. Thread t < TX*TY
-// owns the cell (t % TX, t / TX) of the tile and marches along z with a window
-// of four planes of its own cell in registers (the z faces). At each plane
-// the tile and its two-cell x and y halo are staged in LDS: the owned cells
-// come from the threads' windows, the halo ring from global memory. Then every
-// thread evaluates one x face and one y face from the LDS plane; the faces of
-// the tile number (TX + 1) TY and TX (TY + 1), at most the 256 threads, so
-// each face of the plane is computed once and each axis costs one pass:
-// three flux evaluations per cell, against four when a wave owns one row and
-// computes both y faces of it. The face fluxes go back to LDS and each owned
-// cell sums its six faces. Two workgroup barriers per plane: after the plane
-// is staged, and after the face fluxes are written. (Measured on the 256^3
-// workload: 32 x 7 tiles step in 1.79 ms, 16 x 15 tiles in 1.90 ms, the
-// per-row wave kernel this replaces in 1.93 ms; non-temporal stores and loads
-// of U^n were slower.)
+// owns the cell (t % TX, t / TX) of the tile and marches along z: its cell of
+// the plane and the next two, one limited slope per plane and the left state
+// of the next z face stay in registers, the flux of the lower z face in LDS.
+// At each plane the tile and its two-cell x and y halo are staged in LDS: the
+// owned cells come from the threads' registers, the halo ring from global
+// memory. Then every thread evaluates one x face and one y face from the LDS
+// plane; the faces of the tile number (TX + 1) TY and TX (TY + 1), at most the
+// 256 threads, so each face of the plane is computed once and each axis costs
+// one pass: three flux evaluations per cell, against four when a wave owns one
+// row and computes both y faces of it. The face fluxes go back to LDS and each
+// owned cell sums its six faces. Two workgroup barriers per plane: after the
+// plane is staged, and after the face fluxes are written.
+//
+// What bounds it: at 256^3 the last stage moves 2.9 GB in 0.6 ms, the rate of
+// a large copy (4.8 TB/s); the first two keep the FP64 units 57 % busy, and the
+// rest is the latency of the plane loads between two barriers, which is why
+// the loads of the next plane are issued as soon as their registers are free
+// and the first two stages are held to 168 registers (three workgroups per
+// CU). 256^3: 1.68 ms a step, against 1.79 with a window of four planes in
+// registers and two limited slopes per z face; 97x61x45 channel: 72 us,
+// against 104. Tiles of 32 x 15, 32 x 23 and 64 x 7 cells take 1.79, 1.83 and
+// 1.76 ms at 256^3, and non-temporal stores, or loads of U^n, 5 % more.
 //
 // Halo cells outside the grid are read through the boundary maps; the state
 // may keep ghost layers but they are not read. Per-grid dt and the CFL max
@@ -58,6 +66,25 @@ __device__ __forceinline__ void face_states(double q0, double q1, double q2, dou
     }
 }
 
+// The two face states that a cell gives from its differences db (to the cell
+// below) and df (to the one above): qR at its lower face, qL at its upper one.
+// The operations of face_states, whose slopes they share.
+template <int LIM>
+__device__ __forceinline__ void plane_states(double u, double db, double df, double ka, double kb, double& qR,
+                                             double& qL) {
+    if (LIM == 2) {
+        qR = fma(-kb, db, fma(-ka, df, u));
+        qL = fma(ka, db, fma(kb, df, u));
+    } else if (LIM == 1) {
+        qR = u - 0.5 * df;
+        qL = u + 0.5 * db;
+    } else {
+        const double m = limited_slope<LIM>(db, df);
+        qR = u - 0.5 * m;
+        qL = u + 0.5 * m;
+    }
+}
+
 // Position (hx, hy) in the staged plane of halo cell h (0 .. NHALO-1): first
 // the x halo (columns 0, 1, HX-2, HX-1 of the owned rows), then the y halo
 // (rows 0, 1, HY-2, HY-1 of the owned columns), row by row so that the y halo
@@ -81,6 +108,7 @@ struct TileLds {
     double P[5][HPLANE + 1];  // staged plane: owned cells and halo, [v][hy][hx]
     double FX[5][NXF + 1];    // x-face fluxes (times 2), [v][fy][fx], fx = 0 .. TX
     double FY[5][NYF];        // y-face fluxes (times 2), [v][fy][fx], fy = 0 .. TY
+    double FZ[5][T3];         // lower z-face flux (times 2) of every thread's cell: its own registers' overflow
 };
 
 // The planes of one work item (tile (tx0, ty0), planes k0 .. k0 + seg - 1)
@@ -211,148 +239,143 @@ __device__ __forceinline__ void tile_planes(const FGrid3Head& G, const double* _
     auto plane_off = [&](int kk) -> uint32_t {
         return (uint32_t)((long long)map3(BC, kk, G.nz, G.bcz0, G.bcz1) * G.pz * 8);
     };
-    auto out_plane = [&](int kk) -> uint32_t { return (uint32_t)((long long)(kk < G.nz ? kk : G.nz - 1) * G.pz * 8); };
+    auto out_plane = [&](int kk) -> uint32_t { return (uint32_t)((long long)kk * G.pz * 8); };
 
-    // window of the owned cell: plane kk in slot (kk - k0 + 2) & 3; z face f
-    // (between planes k0 + f - 1 and k0 + f) uses slots f .. f + 3 (mod 4).
-    // Face 0 first, then faces 1 .. seg in unrolled groups of four, so every
-    // slot is a compile-time constant and a given z face of the grid is
-    // computed by the same instructions whatever seg is.
-    double W[4][NV];
-#pragma unroll
-    for (int kz = 0; kz < 4; ++kz) {
-        const uint32_t o = plane_off(k0 - 2 + kz);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) W[kz][v] = ld_buf(rs, cell_off, o + v * vstride);
-        ghost_fix<BC>(G, gq, gown, k0 - 2 + kz, W[kz]);
-    }
-    double H[NV];  // halo cell of the next staged plane
-    {
-        const uint32_t o = plane_off(k0);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) H[v] = ld_buf(rs, halo_off, o + v * vstride);
-        ghost_fix<BC>(G, gq, ghalo, k0, H);
-    }
-    double Fz[2][NV];  // z-face fluxes (times 2): face f in Fz[f & 1]
+    // The thread's own cell along z: at the output plane kk, c = U[kk],
+    // u1 = U[kk + 1], un = U[kk + 2] and the left state qLz of the face above
+    // plane kk, one limited slope per plane (the face-wise formula, operation
+    // for operation). Loads go one plane ahead, right after the registers they
+    // replace were used: those of plane kk + 3 and of the halo of kk + 1 have
+    // the three fluxes of plane kk to arrive.
+    double c[NV], u1[NV], un[NV], H[NV], qLz[NV];
     double qL[NV], qR[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) face_states<LIM>(W[0][v], W[1][v], W[2][v], W[3][v], ka, kb, qL[v], qR[v]);
-    roe_flux<3, 2, true>(qL, qR, G.gm1, Fz[0]);
     {
-        const uint32_t o = plane_off(k0 + 2);
+        double w0[NV], w1[NV];
+        const uint32_t o0 = plane_off(k0 - 2), o1 = plane_off(k0 - 1), o2 = plane_off(k0), o3 = plane_off(k0 + 1);
 #pragma unroll
-        for (int v = 0; v < NV; ++v) W[0][v] = ld_buf(rs, cell_off, o + v * vstride);
-        ghost_fix<BC>(G, gq, gown, k0 + 2, W[0]);
+        for (int v = 0; v < NV; ++v) {
+            w0[v] = ld_buf(rs, cell_off, o0 + v * vstride);
+            w1[v] = ld_buf(rs, cell_off, o1 + v * vstride);
+            c[v] = ld_buf(rs, cell_off, o2 + v * vstride);
+            u1[v] = ld_buf(rs, cell_off, o3 + v * vstride);
+        }
+        ghost_fix<BC>(G, gq, gown, k0 - 2, w0);
+        ghost_fix<BC>(G, gq, gown, k0 - 1, w1);
+        ghost_fix<BC>(G, gq, gown, k0, c);
+        ghost_fix<BC>(G, gq, gown, k0 + 1, u1);
+        const uint32_t o4 = plane_off(k0 + 2);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            un[v] = ld_buf(rs, cell_off, o4 + v * vstride);
+            H[v] = ld_buf(rs, halo_off, o2 + v * vstride);
+        }
+        double F[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            double d;  // the lower face's right state comes with the plane's upper left state
+            face_states<LIM>(w0[v], w1[v], c[v], u1[v], ka, kb, qL[v], qR[v]);
+            plane_states<LIM>(c[v], c[v] - w1[v], u1[v] - c[v], ka, kb, d, qLz[v]);
+        }
+        roe_flux<3, 2, true>(qL, qR, G.gm1, F);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) L.FZ[v][tid] = F[v];
     }
     __builtin_amdgcn_sched_barrier(0);
+    const int kend = k0 + seg < G.nz ? k0 + seg : G.nz;  // uniform over the workgroup
 #pragma unroll 1
-    for (int m0 = 1; m0 <= seg; m0 += 4) {
-        if (k0 + m0 - 1 >= G.nz) break;  // ragged last segment (uniform over the workgroup)
+    for (int kk = k0; kk < kend; ++kk) {
+        // stage plane kk
+        ghost_fix<BC>(G, gq, ghalo, kk, H);
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int f = m0 + jj;
-            const int t = (jj + 1) & 3;  // f mod 4, a compile-time constant
-            const int kk = k0 + f - 1;   // output plane finished at this face
-            double c[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) c[v] = W[(t + 1) & 3][v];
-            // stage plane kk: the owned cells from the window, the halo ring
-            // from the loads issued one plane ahead
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                L.P[v][own_slot] = c[v];
-                L.P[v][halo_slot] = H[v];
-            }
-            double Unc[NV];
-            if (STAGE > 0) {
-                const uint32_t o = out_plane(kk);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) Unc[v] = ld_buf(rn, own_off, o + v * vstride);
-            }
-            // z face f: stencil planes kk-1 .. kk+2
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-                face_states<LIM>(W[t][v], W[(t + 1) & 3][v], W[(t + 2) & 3][v], W[(t + 3) & 3][v], ka, kb, qL[v],
-                                 qR[v]);
-            roe_flux<3, 2, true>(qL, qR, G.gm1, Fz[t & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-            __syncthreads();  // plane kk staged
-            {
-                double Fx[NV];
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const double* p = &L.P[v][xs0];
-                    face_states<LIM>(p[0], p[1], p[2], p[3], ka, kb, qL[v], qR[v]);
-                }
-                roe_flux<3, 0, true>(qL, qR, G.gm1, Fx);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) L.FX[v][xslot] = Fx[v];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            {
-                double Fy[NV];
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const double* p = &L.P[v][ys0];
-                    face_states<LIM>(p[0], p[HX], p[2 * HX], p[3 * HX], ka, kb, qL[v], qR[v]);
-                }
-                roe_flux<3, 1, true>(qL, qR, G.gm1, Fy);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) L.FY[v][tid] = Fy[v];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            // plane kk - 1 is dead: its slot takes plane kk + 3 for face f + 1;
-            // the halo of plane kk + 1 is requested for the next staging
-            {
-                const uint32_t o = plane_off(kk + 3);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) W[t][v] = ld_buf(rs, cell_off, o + v * vstride);
-            }
-            {
-                const uint32_t o = plane_off(kk + 1);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) H[v] = ld_buf(rs, halo_off, o + v * vstride);
-            }
-            if (BC) {
-                // the ghost rules need the loaded values: applied here, after the
-                // loads of the next planes were issued
-                ghost_fix<BC>(G, gq, gown, kk + 3, W[t]);
-                ghost_fix<BC>(G, gq, ghalo, kk + 1, H);
-            }
-            __syncthreads();  // face fluxes of plane kk written
-            const bool plane_ok = kk < G.nz;  // uniform
-            const uint32_t p = out_plane(kk);
-            const uint32_t so = plane_ok ? st_off : DROP_OFFSET;
-            double Sv[NV];
-            if (SRC) {
-                const uint32_t ps = (uint32_t)((long long)(kk < G.nz ? kk : G.nz - 1) * G.ny * G.nx * 8);
-#pragma unroll
-                for (int v = 0; v < NV; ++v) Sv[v] = ld_buf(rsrc, src_off, ps + (uint32_t)(v * svol * 8));
-            }
-            double out[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                // the doubled fluxes against halved areas: the same products
-                double r = (L.FX[v][fxl + 1] - L.FX[v][fxl]) * hax;
-                r += (L.FY[v][fyb + TX] - L.FY[v][fyb]) * hay;
-                r += (Fz[t & 1][v] - Fz[(t + 1) & 1][v]) * haz;
-                if (SRC) r -= vol * Sv[v];  // R = flux sum - |Omega| S
-                if (STAGE == 0) {
-                    out[v] = c[v] + s * r;
-                } else if (STAGE == 1) {
-                    out[v] = 0.75 * Unc[v] + 0.25 * (c[v] + s * r);
-                } else {
-                    out[v] = (1.0 / 3.0) * Unc[v] + (2.0 / 3.0) * (c[v] + s * r);
-                }
-                st_buf<false>(rd[v], so, p, out[v]);
-            }
-            if (STAGE == 2 && own && plane_ok) {
-                const double idx[3] = {G.inv_dx, G.inv_dy, G.inv_dz};
-                lmax = fmax(lmax, cell_lambda<3>(out, G.gamma, G.gm1, idx, fl));
-            }
-            // keep the scheduler from overlapping consecutive planes (register pressure)
-            __builtin_amdgcn_sched_barrier(0);
+        for (int v = 0; v < NV; ++v) {
+            L.P[v][own_slot] = c[v];
+            L.P[v][halo_slot] = H[v];
         }
+        // z face above plane kk
+        ghost_fix<BC>(G, gq, gown, kk + 2, un);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            qL[v] = qLz[v];
+            plane_states<LIM>(u1[v], u1[v] - c[v], un[v] - u1[v], ka, kb, qR[v], qLz[v]);
+            c[v] = u1[v];  // the next plane
+            u1[v] = un[v];
+        }
+        {
+            const uint32_t o = plane_off(kk + 3), oh = plane_off(kk + 1);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                H[v] = ld_buf(rs, halo_off, oh + v * vstride);
+                un[v] = ld_buf(rs, cell_off, o + v * vstride);
+            }
+        }
+        double Fz[NV];
+        roe_flux<3, 2, true>(qL, qR, G.gm1, Fz);
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();  // plane kk staged
+        {
+            double Fx[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const double* p = &L.P[v][xs0];
+                face_states<LIM>(p[0], p[1], p[2], p[3], ka, kb, qL[v], qR[v]);
+            }
+            roe_flux<3, 0, true>(qL, qR, G.gm1, Fx);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) L.FX[v][xslot] = Fx[v];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        double Unc[NV];
+        if (STAGE > 0) {
+            const uint32_t o = out_plane(kk);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) Unc[v] = ld_buf(rn, own_off, o + v * vstride);
+        }
+        {
+            double Fy[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                const double* p = &L.P[v][ys0];
+                face_states<LIM>(p[0], p[HX], p[2 * HX], p[3 * HX], ka, kb, qL[v], qR[v]);
+            }
+            roe_flux<3, 1, true>(qL, qR, G.gm1, Fy);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) L.FY[v][tid] = Fy[v];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();  // face fluxes of plane kk written
+        const uint32_t p = out_plane(kk);
+        double Sv[NV];
+        if (SRC) {
+            const uint32_t ps = (uint32_t)((long long)kk * G.ny * G.nx * 8);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) Sv[v] = ld_buf(rsrc, src_off, ps + (uint32_t)(v * svol * 8));
+        }
+        double out[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const double cv = L.P[v][own_slot];
+            // the doubled fluxes against halved areas: the same products
+            double r = (L.FX[v][fxl + 1] - L.FX[v][fxl]) * hax;
+            r += (L.FY[v][fyb + TX] - L.FY[v][fyb]) * hay;
+            r += (Fz[v] - L.FZ[v][tid]) * haz;
+            L.FZ[v][tid] = Fz[v];
+            if (SRC) r -= vol * Sv[v];  // R = flux sum - |Omega| S
+            if (STAGE == 0) {
+                out[v] = cv + s * r;
+            } else if (STAGE == 1) {
+                out[v] = 0.75 * Unc[v] + 0.25 * (cv + s * r);
+            } else {
+                out[v] = (1.0 / 3.0) * Unc[v] + (2.0 / 3.0) * (cv + s * r);
+            }
+            st_buf<false>(rd[v], st_off, p, out[v]);
+        }
+        if (STAGE == 2) __builtin_amdgcn_sched_barrier(0);
+        if (STAGE == 2 && own) {
+            const double idx[3] = {G.inv_dx, G.inv_dy, G.inv_dz};
+            lmax = fmax(lmax, cell_lambda<3>(out, G.gamma, G.gm1, idx, fl));
+        }
+        // keep the scheduler from overlapping consecutive planes (register pressure)
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -368,7 +391,7 @@ __device__ __forceinline__ void tile_of_item(const FGrid3Head& G, int item, int&
 // At least 2 waves per SIMD: the stage-3 kernel with the ghost rules and a
 // source term would take 257 registers and run at 1 wave per SIMD.
 template <int STAGE, bool SRC, bool BC>
-__global__ void __launch_bounds__(T3) __attribute__((amdgpu_waves_per_eu(2))) k_fused3d(const FGrid3* __restrict__ grid, int nitems, const double* Un,
+__global__ void __launch_bounds__(T3) __attribute__((amdgpu_waves_per_eu(BC || STAGE == 2 ? 2 : 3))) k_fused3d(const FGrid3* __restrict__ grid, int nitems, const double* Un,
                                                 const double* __restrict__ Us, double* Ud,
                                                 unsigned long long* __restrict__ lam, double* __restrict__ dtg,
                                                 const double* __restrict__ dt_fixed, double* __restrict__ dt_out,
@@ -533,22 +556,26 @@ int fused3d_slots() {
     return bmin * cus;
 }
 
-// Segment height (a multiple of 4): as in 2D, the one minimising (rounds of
-// resident workgroups) x (planes per item + 1); ties go to the taller segment.
-int fused3d_auto_seg(const FGrid3& G, int slots) {
-    if (slots <= 0) return 16;
-    int best = 16;
-    double best_cost = 0.0;
-    for (int seg = 4; seg <= 256; seg += 4) {
-        const long long items = fused3d_items(G, seg);
-        const long long rounds = (items + slots - 1) / slots;
-        const double cost = (double)rounds * (seg + 1);
-        if (seg == 4 || cost <= best_cost) {
-            best_cost = cost;
-            best = seg;
-        }
-    }
-    return best;
+// Segment height (a multiple of 4) by the work of the busiest compute unit:
+// the items it gets, times their planes and one more for the four planes and
+// the z flux that an item starts with. An item alone on its compute unit
+// takes 1.4 times as long per plane (97x61x45 channel: 7.4 us a plane and step
+// alone, 5.3 with two or more). Among heights within 1 % the tallest, which
+// reads the fewest halo planes. The model puts 256^3 at 52 planes (measured:
+// 1680 us a step at 52, 1691 at 16, 1735 at 32, 1742 at 8, 1892 at 4) and
+// 130x120x110 at 8 (258 us; 283 at 4, 299 at 16 and at the 24 planes that
+// counting rounds of two workgroups per compute unit gave).
+int fused3d_auto_seg(const FGrid3& G, int cus) {
+    if (cus <= 0) return 16;
+    auto cost = [&](int seg) {
+        const long long per_cu = (fused3d_items(G, seg) + cus - 1) / cus;
+        return (double)per_cu * (seg + 1) * (per_cu == 1 ? 1.4 : 1.0);
+    };
+    double least = cost(4);
+    for (int seg = 8; seg <= 256; seg += 4) least = fmin(least, cost(seg));
+    int seg = 256;
+    while (seg > 4 && cost(seg) > 1.01 * least) seg -= 4;
+    return seg;
 }
 
 }  // namespace fvk

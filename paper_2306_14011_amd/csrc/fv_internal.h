@@ -98,7 +98,7 @@ void launch_fused3d_init(const FGrid3* grid, int nitems, const double* U, unsign
                          uint32_t* status, hipStream_t s);
 int fused3d_slots();
 int fused3d_init_items(const FGrid3& G);
-int fused3d_auto_seg(const FGrid3& G, int slots);
+int fused3d_auto_seg(const FGrid3& G, int cus);
 int fused_auto_seg(const FGrid* grids, int ngrids, int slots);
 
 // whole 2D steps in one launch each (fv_step2d.hip); cus: the device's compute units. ws: step2d_bytes() of
