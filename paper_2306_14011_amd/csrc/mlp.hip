@@ -1,5 +1,6 @@
 // FP32 kernels of the launch-parameter autotuner's regression network:
-// training (forward, backward and Adam over minibatches, one workgroup),
+// training (forward, backward and Adam over minibatches, one workgroup per 64
+// rows of a minibatch, at most eight),
 // loss/gradient, prediction, and the exhaustive sweep of the launch space
 // with a top-k selection of the lowest predicted runtimes.
 //
@@ -42,9 +43,9 @@ constexpr int NP_MAX = Lay<FV_MLP_IN_SIZED>::NP;
 constexpr int MAXN = 65536;
 
 // Bytes of scratch that callers pass for n rows. The kernels keep the network,
-// the activations and the moments on the chip and use none of it; the size
-// stays what callers ask for and check.
-inline size_t scratch_bytes(int n) { return ((size_t)5 * n * H + 2 * (size_t)n + NP_MAX) * sizeof(float) + 256; }
+// the activations and the moments on the chip; training over several
+// workgroups exchanges its sums there.
+constexpr size_t scratch_bytes(int n) { return ((size_t)5 * n * H + 2 * (size_t)n + NP_MAX) * sizeof(float) + 256; }
 
 __device__ __forceinline__ float relu(float z) { return z > 0.f ? z : 0.f; }
 
@@ -52,16 +53,17 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------------------
-// Training and gradient: one workgroup of eight waves, two per SIMD.
+// Training and gradient: workgroups of eight waves, two per SIMD.
 //
 // The work of a minibatch is three small matrix products per layer (forward,
-// delta, weight gradient) that depend on each other, so one workgroup's matrix
-// cores bound it: 200 rows are 11 MFLOP, 18 us at a CU's 256 FP32 operations a
-// clock. Everything stays on the chip: the weights and the activations of 128
+// delta, weight gradient) that depend on each other, so the matrix cores of a
+// workgroup's CU bound it: 200 rows are 11 MFLOP, 18 us at 256 FP32 operations
+// a clock. Everything stays on the chip: the weights and the activations of 128
 // rows in LDS, gradients and Adam moments in the registers of the lane that
 // holds their sum, so the update needs no exchange. Measured: 200-row
-// minibatches in 34 us against 530 us for one thread per element with
-// activations and gradients in global memory.
+// minibatches in 33 us on one workgroup (18 on four, see Exchange) against
+// 530 us for one thread per element with activations and gradients in global
+// memory.
 //
 // Rows go in chunks of 128 (four tiles of 32). Wave w takes tile w / 2 and
 // neurons 32 (w % 2) .. + 31 of every layer: transposed products Z^T = W H^T
@@ -389,15 +391,120 @@ __global__ void __launch_bounds__(TT) k_loss_grad(const float* __restrict__ P, c
     if (threadIdx.x == 0) *loss = t;
 }
 
+// A minibatch over several workgroups: each takes a share of its rows, all sum
+// the shares' gradients in the order of the ranks and make the same Adam step,
+// so that each has the whole network and takes the same decision to stop (the
+// sums, and with them every later value, are the same bits in all).
+// Bound by the chain forward - backward - exchange - update: 64 rows take 13 us
+// on one workgroup, of which some 6 are matrix products, and the exchange of
+// 43 KB a workgroup through the last-level cache 4.6 us more, so that a
+// workgroup takes up to 64 rows before another is added. 200-row minibatches:
+// 33.3 us on one workgroup, 22.1 on two, 17.7 on four; 500 rows 73, 42, 26, and
+// 21.5 on eight; 128 rows 20.5, and 16.1 on two. (Fences in every thread in
+// place of one cost 2.4 us more, and 64 rows then took 13.0 us on one and 16.8
+// on two. All workgroups on one XCD take 1 us less, but would queue the
+// trainings of several streams on its 32 CUs.)
+// The waits end: a launch's at most eight workgroups are dispatched in order,
+// each to a CU of its own, go through the same minibatches, and none waits for
+// anything but the others' counts. Rank r goes to XCD r, so that 32 launches
+// are resident whole before one could be in part, and hardware queues are
+// fewer.
+constexpr int MAX_WGS = 8;
+constexpr int WG_ROWS = 64;
+
+inline int train_workgroups(int batch) {
+    const int w = (batch + WG_ROWS - 1) / WG_ROWS;
+    return w < MAX_WGS ? w : MAX_WGS;
+}
+
+// Exchange buffer, in the caller's scratch (from a multiple of 64 bytes on): two
+// counters, then per workgroup its sums of a minibatch as every lane holds
+// them: four vectors of four, and for the lanes of the first four waves two
+// more and two values.
+constexpr size_t EX_HEAD = 256;
+constexpr size_t EX_ROW = TT * 16;                                // bytes of a vector of every lane
+constexpr size_t EX_BYTES = 4 * EX_ROW + TT / 2 * (16 + 16 + 8);  // 43008 per workgroup
+constexpr bool exchange_fits() {
+    for (int w = 2; w <= MAX_WGS; ++w)
+        if (64 + EX_HEAD + w * EX_BYTES > scratch_bytes(WG_ROWS * (w - 1) + 1)) return false;
+    return true;
+}
+static_assert(exchange_fits(), "the scratch of the smallest batch for a number of workgroups holds their sums");
+
+struct Exchange {
+    char* base;
+    int rank, size;
+    unsigned sent, taken;  // what the counters reach when all have written, and have read, a minibatch's sums
+
+    __device__ static void wait(unsigned* ctr, unsigned count) {
+        while ((int)(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - count) < 0)
+            __builtin_amdgcn_s_sleep(1);
+    }
+    // Sums g over the workgroups, in the order of their ranks, in all of them.
+    __device__ void sum(Grads& g) {
+        unsigned* const ctr = (unsigned*)base;
+        const int tid = threadIdx.x;
+        const bool first4 = tid < TT / 2;  // uniform over a wave
+        char* const out = base + EX_HEAD + rank * EX_BYTES + tid * 16;
+        if (tid == 0) wait(ctr + 32, taken);  // every workgroup has read the previous minibatch's sums
+        __syncthreads();
+        *(v4f*)out = g.w3[0];
+        *(v4f*)(out + EX_ROW) = g.w3[1];
+        *(v4f*)(out + 2 * EX_ROW) = g.w2[0];
+        *(v4f*)(out + 3 * EX_ROW) = g.w2[1];
+        if (first4) {
+            *(v4f*)(out + 4 * EX_ROW) = g.w1;
+            *(v4f*)(out + 4 * EX_ROW + TT / 2 * 16) = v4f{g.b1, g.b2, g.b3, g.w4};
+            *(float2*)(base + EX_HEAD + rank * EX_BYTES + 4 * EX_ROW + TT * 16 + tid * 8) = float2{g.b4, g.sq};
+        }
+        __syncthreads();
+        sent += size;
+        taken += size;
+        if (tid == 0) {
+            __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            wait(ctr, sent);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        __syncthreads();
+        g.clear();
+#pragma unroll 1
+        for (int r = 0; r < size; ++r) {
+            const char* const in = base + EX_HEAD + r * EX_BYTES + tid * 16;
+            g.w3[0] += *(const v4f*)in;
+            g.w3[1] += *(const v4f*)(in + EX_ROW);
+            g.w2[0] += *(const v4f*)(in + 2 * EX_ROW);
+            g.w2[1] += *(const v4f*)(in + 3 * EX_ROW);
+            if (first4) {
+                g.w1 += *(const v4f*)(in + 4 * EX_ROW);
+                const v4f b = *(const v4f*)(in + 4 * EX_ROW + TT / 2 * 16);
+                g.b1 += b[0];
+                g.b2 += b[1];
+                g.b3 += b[2];
+                g.w4 += b[3];
+                const float2 c = *(const float2*)(base + EX_HEAD + r * EX_BYTES + 4 * EX_ROW + TT * 16 + tid * 8);
+                g.b4 += c.x;
+                g.sq += c.y;
+            }
+        }
+        __syncthreads();
+        if (tid == 0) __hip_atomic_fetch_add(ctr + 32, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+
+// Clears the counters (a kernel, so that the call can be captured in a graph).
+__global__ void k_train_clear(unsigned* ctr) { ctr[threadIdx.x] = 0; }
+
 template <int IN>
 __global__ void __launch_bounds__(TT) k_train(float* P, float* M, float* V, int32_t* tptr, const float* __restrict__ X,
                                               const float* __restrict__ Y, int n, const int32_t* __restrict__ order,
-                                              fv_mlp_hparams hp, float* epoch_loss, int32_t* epochs_run) {
+                                              fv_mlp_hparams hp, float* epoch_loss, int32_t* epochs_run, char* exchange) {
     __shared__ TrainLds S;
+    const int rank = blockIdx.x, size = gridDim.x;
     if (hp.max_epochs <= 0) {
-        if (threadIdx.x == 0) *epochs_run = 0;
+        if (rank == 0 && threadIdx.x == 0) *epochs_run = 0;
         return;
     }
+    Exchange ex{exchange, rank, size, 0, 0};
     int t = *tptr;
     // running powers of the decay factors for the bias correction
     double p1 = pow((double)hp.beta1, (double)t), p2 = pow((double)hp.beta2, (double)t);
@@ -412,24 +519,37 @@ __global__ void __launch_bounds__(TT) k_train(float* P, float* M, float* V, int3
     float best = FLT_MAX;
     int noimp = 0;
     int e = 0;
+    // This workgroup's rows of a minibatch of sz rows: part of them, from lo.
+    auto lo = [&](int sz) { return (int)((long long)sz * rank / size); };
+    auto part = [&](int sz) { return (int)((long long)sz * (rank + 1) / size) - lo(sz); };
     RowFetch<IN> next;
-    next.load(X, Y, order, 0, min(hp.batch, n));
+    {
+        const int sz = min(hp.batch, n);
+        next.load(X, Y, order, lo(sz), part(sz));
+    }
     for (; e < hp.max_epochs; ++e) {
         float acc = 0.f;  // this lane's part of the epoch's loss
         const int32_t* rows = order + (size_t)e * n;
         for (int start = 0; start < n; start += hp.batch) {
-            const int sz = min(hp.batch, n - start);
+            const int sz = min(hp.batch, n - start), own = part(sz);
             const float inv = 1.0f / (float)sz;
             g.clear();
-            for (int c = 0; c < sz; c += CROWS) {
+            for (int c = 0; c == 0 || c < own; c += CROWS) {
                 next.store(S);
                 __syncthreads();
                 // the following chunk: of this minibatch, of the next one, or of the next epoch
-                if (c + CROWS < sz) next.load(X, Y, rows, start + c + CROWS, sz - c - CROWS);
-                else if (start + sz < n) next.load(X, Y, rows, start + sz, min(hp.batch, n - start - sz));
-                else if (e + 1 < hp.max_epochs) next.load(X, Y, rows + n, 0, min(hp.batch, n));
-                train_chunk(S, min(CROWS, sz - c), inv, g);
+                if (c + CROWS < own) {
+                    next.load(X, Y, rows, start + lo(sz) + c + CROWS, own - c - CROWS);
+                } else if (start + sz < n) {
+                    const int nsz = min(hp.batch, n - start - sz);
+                    next.load(X, Y, rows, start + sz + lo(nsz), part(nsz));
+                } else if (e + 1 < hp.max_epochs) {
+                    const int nsz = min(hp.batch, n);
+                    next.load(X, Y, rows + n, lo(nsz), part(nsz));
+                }
+                train_chunk(S, min(CROWS, own - c), inv, g);
             }
+            if (size > 1) ex.sum(g);
             ++t;
             p1 *= (double)hp.beta1;
             p2 *= (double)hp.beta2;
@@ -449,7 +569,7 @@ __global__ void __launch_bounds__(TT) k_train(float* P, float* M, float* V, int3
             // (the next chunk's barrier publishes the new weights)
         }
         const float el = block_sum(S, acc) / (float)n;
-        if (threadIdx.x == 0) epoch_loss[e] = el;
+        if (rank == 0 && threadIdx.x == 0) epoch_loss[e] = el;
         if (el > best - hp.tol) ++noimp;
         else noimp = 0;
         if (el < best) best = el;
@@ -458,6 +578,7 @@ __global__ void __launch_bounds__(TT) k_train(float* P, float* M, float* V, int3
             break;
         }
     }
+    if (rank != 0) return;
     g.clear();
     each_owned<IN>(S, g, [&](int k, const float* p, int at, float, bool) {
         P[at] = *p;
@@ -938,12 +1059,15 @@ int fv_mlp_train(float* params, int32_t n_in, float* adam_m, float* adam_v, int3
         return FV_EINVAL;
     const int bmax = hp->batch < n ? hp->batch : n;
     if (ws_bytes < mlp::scratch_bytes(bmax)) return FV_EWORKSPACE;
+    const int wgs = mlp::train_workgroups(bmax);
+    char* const ex = (char*)(((uintptr_t)workspace + 63) & ~(uintptr_t)63);
+    if (wgs > 1) hipLaunchKernelGGL(mlp::k_train_clear, dim3(1), dim3(64), 0, (hipStream_t)stream, (unsigned*)ex);
     if (n_in == FV_MLP_IN)
-        hipLaunchKernelGGL(mlp::k_train<FV_MLP_IN>, dim3(1), dim3(mlp::TT), 0, (hipStream_t)stream, params, adam_m,
-                           adam_v, adam_t, X, y, n, order, *hp, epoch_loss, epochs_run);
+        hipLaunchKernelGGL(mlp::k_train<FV_MLP_IN>, dim3(wgs), dim3(mlp::TT), 0, (hipStream_t)stream, params, adam_m,
+                           adam_v, adam_t, X, y, n, order, *hp, epoch_loss, epochs_run, ex);
     else
-        hipLaunchKernelGGL(mlp::k_train<FV_MLP_IN_SIZED>, dim3(1), dim3(mlp::TT), 0, (hipStream_t)stream, params,
-                           adam_m, adam_v, adam_t, X, y, n, order, *hp, epoch_loss, epochs_run);
+        hipLaunchKernelGGL(mlp::k_train<FV_MLP_IN_SIZED>, dim3(wgs), dim3(mlp::TT), 0, (hipStream_t)stream, params,
+                           adam_m, adam_v, adam_t, X, y, n, order, *hp, epoch_loss, epochs_run, ex);
     return mlp_check_launch();
 }
 
