@@ -685,11 +685,14 @@ static int set_fused_stage(fv_ctx* c, int st, int32_t seg, int32_t waves) {
         G.nu_fac = c->g.nu_fac;
         c->fauto[st] = fvk::fused_auto_seg(&G, 1, fvk::fused_slots());
         if (seg == 0) seg = c->fauto[st];
-        G.seg = seg;
+        // the library's own height stands for its own split of the rows
+        G.seg = seg == c->fauto[st] && waves == 0
+                    ? fvk::fused_rows(G, seg, c->cus, c->g.met || c->g.mu > 0.0 ? 2 : 3)
+                    : seg;
         c->hgrid = G;
         e = hipMemcpyAsync(c->fgrid[st], &G, sizeof(G), hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        c->fitems[st] = fvk::fused_items(G, seg);
+        c->fitems[st] = fvk::fused_items(G, G.seg);
     }
     if (e != hipSuccess) return fail(c, FV_EDEVICE, "grid table upload failed: %s", hipGetErrorString(e));
     c->fseg[st] = seg;

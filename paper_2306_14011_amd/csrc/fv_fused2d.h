@@ -261,9 +261,9 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
     // ka D[r] + kb D[r+1] and kb D[r] + ka D[r+1]), so each row needs one new
     // difference and one minmod, and the face's left state is carried from
     // the previous face. The same values as the face-wise formula, operation
-    // for operation (minmod is symmetric); since r0 is a multiple of 4, a
-    // given face of the grid is computed by the same instructions whatever
-    // the segment height.
+    // for operation (minmod is symmetric); the four rows of a group are the
+    // same instructions, so a given face of the grid has the same bits
+    // whatever the segment height.
     double W[4][NV];
     double wxp[2];  // curvilinear variant: x wall normal of the row loaded last
 #pragma unroll
@@ -357,6 +357,7 @@ __device__ __forceinline__ void fused2d_rows(const FGridHead& G, const double* _
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int f = m0 + j;
+            if (j > 0 && f > seg) break;  // uniform
             const int t = (j + 1) & 3;  // f mod 4, a compile-time constant
             const int rr = r0 + f - 1;  // output row finished at this face
             // rows rr-1 .. rr+2 sit in slots t .. t+3; row rr-1 is no longer

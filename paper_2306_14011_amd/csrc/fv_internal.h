@@ -100,6 +100,7 @@ int fused3d_slots();
 int fused3d_init_items(const FGrid3& G);
 int fused3d_auto_seg(const FGrid3& G, int cus);
 int fused_auto_seg(const FGrid* grids, int ngrids, int slots);
+int fused_rows(const FGrid& G, int seg, int cus, int per_simd);
 
 // whole 2D steps in one launch each (fv_step2d.hip); cus: the device's compute units. ws: step2d_bytes() of
 // scratch; step: the step's number in the call; launch_step2d_init: the first
