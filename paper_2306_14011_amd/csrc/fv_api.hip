@@ -519,7 +519,7 @@ static bool has_walls(const fv_ctx* c) {
 static int fused_step3(fv_ctx* c, double* U, int32_t nsteps, const double* dt_in, double* dt_out) {
     const fvk::FGrid3* const* G = (const fvk::FGrid3* const*)c->fgrid;
     const bool walls = has_walls(c);
-    unsigned long long* first = fvk::lam_first(c->flam, 1);
+    unsigned long long* first = fvk::lam_first(c->flam);
     fvk::launch_fused3d_init(G[0], c->finit, U, first, c->status, c->stream);
     for (int32_t s = 0; s < nsteps; ++s) {
         {
@@ -586,7 +586,7 @@ static int fused_step(fv_ctx* c, double* U, int32_t nsteps, const double* dt_in,
     if (c->g.ndim == 3) return fused_step3(c, U, nsteps, dt_in, dt_out);
     if (whole_step(c)) return whole_steps(c, U, nsteps, dt_in, dt_out);
     const int walls = c->g.met ? 3 : (c->g.mu > 0.0 ? 2 : (has_walls(c) ? 1 : 0));
-    unsigned long long* first = fvk::lam_first(c->flam, 1);
+    unsigned long long* first = fvk::lam_first(c->flam);
     fvk::launch_fused_init(c->fgrid[0], 1, c->fitems[0], U, first, c->status, c->stream, c->g.met);
     for (int32_t s = 0; s < nsteps; ++s) {
         {
@@ -687,7 +687,7 @@ static int set_fused_stage(fv_ctx* c, int st, int32_t seg, int32_t waves) {
         if (seg == 0) seg = c->fauto[st];
         // the library's own height stands for its own split of the rows
         G.seg = seg == c->fauto[st] && waves == 0
-                    ? fvk::fused_rows(G, seg, c->cus, c->g.met || c->g.mu > 0.0 ? 2 : 3)
+                    ? fvk::fused_rows(&G, 1, seg, c->cus, c->g.met || c->g.mu > 0.0 ? 2 : 3)
                     : seg;
         c->hgrid = G;
         e = hipMemcpyAsync(c->fgrid[st], &G, sizeof(G), hipMemcpyHostToDevice, c->stream);

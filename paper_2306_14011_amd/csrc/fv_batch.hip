@@ -146,6 +146,12 @@ int validate_batch(int32_t ngrids, const fv_grid_desc* grids, BLayout* L, char* 
 
 struct fv_batch {
     int ngrids, waves, nitems, order;
+    bool own;  // the heights are the library's
+    // Parts of the table that are advanced one after the other (one unless own).
+    struct Group {
+        int first, ngrids, nitems;
+    };
+    std::vector<Group> groups;
     int mode;  // stage-kernel variant: 0 periodic / transmissive, 1 walls or inflow faces, 2 viscous
     hipStream_t stream, cap;
     fvk::FGrid* grids;
@@ -190,25 +196,62 @@ static void drop_graph(fv_batch* b) {
     b->graph_history = nullptr;
 }
 
+// Enqueues the three stages of a step of the grids of group q.
+static void enqueue_stages(fv_batch* b, const fv_batch::Group& q, double* U, unsigned long long* clk, hipStream_t s) {
+    const fvk::FGrid* grids = b->grids + q.first;
+    fvk::launch_fused_stage(0, b->waves, grids, q.ngrids, q.nitems, U, U, b->U1, b->lam, b->dt, nullptr, nullptr,
+                            b->status, clk, s, nullptr, b->mode);
+    fvk::launch_fused_stage(1, b->waves, grids, q.ngrids, q.nitems, U, b->U1, b->U2, b->lam, b->dt, nullptr, nullptr,
+                            b->status, clk, s, nullptr, b->mode);
+    fvk::launch_fused_stage(2, b->waves, grids, q.ngrids, q.nitems, U, b->U2, U, b->lam, b->dt, nullptr, nullptr,
+                            b->status, clk, s, nullptr, b->mode);
+}
+
 // Enqueues one step (three stages, plus the clock record when timing) on s.
 static void enqueue_step(fv_batch* b, double* U, hipStream_t s) {
     const int nclk = 6 * b->ngrids;
     unsigned long long* clk = b->history ? b->clk : nullptr;
     if (clk) hipLaunchKernelGGL(k_clk_reset, dim3(1), dim3(256), 0, s, b->clk, nclk);
-    fvk::launch_fused_stage(0, b->waves, b->grids, b->ngrids, b->nitems, U, U, b->U1, b->lam, b->dt, nullptr,
-                            nullptr, b->status, clk, s, nullptr, b->mode);
-    fvk::launch_fused_stage(1, b->waves, b->grids, b->ngrids, b->nitems, U, b->U1, b->U2, b->lam, b->dt,
-                            nullptr, nullptr, b->status, clk, s, nullptr, b->mode);
-    fvk::launch_fused_stage(2, b->waves, b->grids, b->ngrids, b->nitems, U, b->U2, U, b->lam, b->dt, nullptr,
-                            nullptr, b->status, clk, s, nullptr, b->mode);
+    for (const fv_batch::Group& q : b->groups) enqueue_stages(b, q, U, clk, s);
     if (clk) hipLaunchKernelGGL(k_clk_store, dim3(1), dim3(256), 0, s, b->clk, nclk, b->history, b->max_steps, b->counter);
 }
 
 static bool valid_seg(int32_t seg) { return seg >= 4 && seg <= 1024 && seg % 4 == 0; }
 
-// Orders the table by the work-list order, assigns each grid its segment
-// height and first work item, and uploads it. Work items of a grid are
-// contiguous; the step's graph is rebuilt on the next step.
+// Splits the grids into the least number of groups that 24-row items of each
+// fill the device's resident waves (cap) at most once, evenly: the largest
+// grid left goes to the group with the least work. part[g]: the group of grid g.
+static int split_groups(const std::vector<fvk::FGrid>& grids, long long cap, std::vector<int>& part) {
+    const int n = (int)grids.size();
+    part.assign(n, 0);
+    auto items = [&](int g) { return (long long)fvk::fused_items(grids[g], 24); };
+    long long total = 0;
+    for (int g = 0; g < n; ++g) total += items(g);
+    if (cap <= 0 || total <= cap) return 1;
+    std::vector<int> perm(n);
+    std::iota(perm.begin(), perm.end(), 0);
+    std::stable_sort(perm.begin(), perm.end(), [&](int a, int c) { return items(a) > items(c); });
+    const int k = (int)((total + cap - 1) / cap < n ? (total + cap - 1) / cap : n);
+    std::vector<long long> load(k, 0);
+    for (int g : perm) {
+        const int q = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+        part[g] = q;
+        load[q] += items(g);
+    }
+    return k;
+}
+
+// Orders the table by group and work-list order, assigns each grid its segment
+// height and first work item (counted within its group), and uploads it. Work
+// items of a grid are contiguous; the step's graph is rebuilt on the next step.
+//
+// With the heights at the library's choice, a batch of more than one round of
+// resident waves is advanced in groups of one round each, all steps of a group
+// before the next: the waves of a round march in step, so that the halo rows
+// they share are still in L2, and a group's states stay in the last-level
+// cache from stage to stage. 96 grids of 128 to 1024 cells a side (30M cells),
+// 8 steps: 14.3 ms in one group, 13.2 in eight of one round each, 13.7 in
+// seven, 13.5 in ten.
 static int apply_schedule(fv_batch* b, int32_t order) {
     const int n = b->ngrids;
     std::vector<int> perm(n);
@@ -217,15 +260,38 @@ static int apply_schedule(fv_batch* b, int32_t order) {
         std::stable_sort(perm.begin(), perm.end(), [&](int a, int c) {
             return (long long)b->by_grid[a].nx * b->by_grid[a].ny > (long long)b->by_grid[c].nx * b->by_grid[c].ny;
         });
-    b->host_grids.resize(n);
-    long long work = 0;
-    for (int q = 0; q < n; ++q) {
-        fvk::FGrid G = b->by_grid[perm[q]];
-        G.work0 = (int)work;
-        work += fvk::fused_items(G, G.seg);
-        b->host_grids[q] = G;
+    std::vector<int> part(n, 0);
+    int k = 1, cus = 0;
+    const int per_simd = b->mode == 2 ? 2 : 3;  // resident waves
+    if (b->own) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            cus = 0;
+        k = split_groups(b->by_grid, 4LL * cus * per_simd, part);
     }
-    if (work > 0x7fffffff) return bfail(b, FV_EINVAL, "too many work items");
+    std::vector<fvk::FGrid> table;
+    std::vector<fv_batch::Group> groups;
+    long long work = 0;
+    for (int q = 0; q < k; ++q) {
+        const int first = (int)table.size();
+        for (int g : perm)
+            if (part[g] == q) table.push_back(b->by_grid[g]);
+        fvk::FGrid* grids = table.data() + first;
+        const int count = (int)table.size() - first;
+        const int rows = b->own ? fvk::fused_rows(grids, count, grids[0].seg, cus, per_simd) : 0;
+        long long own = 0;
+        for (int i = 0; i < count; ++i) {
+            if (rows) grids[i].seg = rows;
+            grids[i].work0 = (int)own;
+            own += fvk::fused_items(grids[i], grids[i].seg);
+        }
+        work += own;
+        if (work > 0x7fffffff) return bfail(b, FV_EINVAL, "too many work items");
+        groups.push_back({first, count, (int)own});
+    }
+    b->host_grids.swap(table);
+    b->groups.swap(groups);
     b->nitems = (int)work;
     b->order = order;
     hipError_t e = hipMemcpyAsync(b->grids, b->host_grids.data(), sizeof(fvk::FGrid) * n, hipMemcpyHostToDevice,
@@ -319,6 +385,7 @@ int fv_batch_create(int32_t ngrids, const fv_grid_desc* grids, int32_t seg, int3
                 if ((d.bc[a][sd] == FV_BC_WALL || d.bc[a][sd] == FV_BC_INFLOW) && b->mode < 1) b->mode = 1;
         if (d.mu > 0.0) b->mode = 2;
     }
+    b->own = seg == 0 && waves == 0;
     if (seg == 0) seg = fvk::fused_auto_seg(b->by_grid.data(), ngrids, fvk::fused_slots());
     for (int g = 0; g < ngrids; ++g) b->by_grid[g].seg = seg;
     hipError_t e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
@@ -344,6 +411,16 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps) {
     if (!U || nsteps < 0) return bfail(b, FV_EINVAL, "null state or negative step count");
     if (nsteps == 0) return FV_OK;
     const bool timed = b->history != nullptr;
+    if (b->groups.size() > 1 && !timed) {
+        // launches of a full round each: no graph needed to hide them
+        fvk::launch_lam_reset(b->lam, b->ngrids, b->stream);
+        for (const fv_batch::Group& q : b->groups) {
+            fvk::launch_fused_init(b->grids + q.first, q.ngrids, q.nitems, U, b->lam, b->status, b->stream);
+            for (int32_t s = 0; s < nsteps; ++s) enqueue_stages(b, q, U, nullptr, b->stream);
+        }
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? FV_OK : bfail(b, FV_EDEVICE, hipGetErrorString(e));
+    }
     if (b->graph_U != U || !b->exec || b->graph_timed != timed || b->graph_history != b->history) {
         drop_graph(b);
         hipError_t e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeRelaxed);
@@ -367,7 +444,8 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps) {
         b->graph_history = b->history;
     }
     fvk::launch_lam_reset(b->lam, b->ngrids, b->stream);
-    fvk::launch_fused_init(b->grids, b->ngrids, b->nitems, U, b->lam, b->status, b->stream);
+    for (const fv_batch::Group& q : b->groups)
+        fvk::launch_fused_init(b->grids + q.first, q.ngrids, q.nitems, U, b->lam, b->status, b->stream);
     for (int32_t s = 0; s < nsteps;) {
         const bool many = nsteps - s >= GRAPH_STEPS;
         hipError_t e = hipGraphLaunch(many ? b->exec_many : b->exec, b->stream);
@@ -416,8 +494,10 @@ int fv_batch_set_schedule(fv_batch* b, const int32_t* segs, int32_t order) {
     if (segs)
         for (int g = 0; g < b->ngrids; ++g)
             if (!valid_seg(segs[g])) return bfail(b, FV_EINVAL, "seg must be a multiple of 4 in [4, 1024]");
-    if (segs)
+    if (segs) {
         for (int g = 0; g < b->ngrids; ++g) b->by_grid[g].seg = segs[g];
+        b->own = false;
+    }
     return apply_schedule(b, order);
 }
 

@@ -163,7 +163,8 @@ int fused_auto_seg(const FGrid* grids, int ngrids, int slots) {
     return best;
 }
 
-// Rows per item that a grid is split into where the height is the library's:
+// Rows per item that a set of grids is split into where the height is the
+// library's:
 // fused_auto_seg counts rounds of resident waves in steps of four rows, but a
 // SIMD whose last wave arrives late finishes late, whatever the rest does. So,
 // up to grids that 24-row items fill once, the height (2 .. 24) minimises the
@@ -176,13 +177,18 @@ int fused_auto_seg(const FGrid* grids, int ngrids, int slots) {
 // 768^2 47.6 and 43.8, 1024^2 74.7 and 68.0, 1500x1100 channel 116 and 104;
 // viscous 1024^2 94 and 80, 1500^2 165 and 144; curvilinear 768^2 75 and 64,
 // 3328x1024 329 and 309. At 2048^2 both give 24 rows.
-int fused_rows(const FGrid& G, int seg, int cus, int per_simd) {
+int fused_rows(const FGrid* grids, int ngrids, int seg, int cus, int per_simd) {
     const long long simds = 4LL * cus;
-    if (cus <= 0 || fused_items(G, 24) > 3 * simds) return seg;
+    auto items = [&](int rows) {
+        long long n = 0;
+        for (int g = 0; g < ngrids; ++g) n += (long long)fused_items(grids[g], rows);
+        return n;
+    };
+    if (cus <= 0 || items(24) > 3 * simds) return seg;
     int best = seg;
     double best_cost = 0.0;
     for (int rows = 24; rows >= 2; --rows) {
-        const long long p = (fused_items(G, rows) + simds - 1) / simds;
+        const long long p = (items(rows) + simds - 1) / simds;
         const double waves = p == 1 ? 1.4 : (p == 2 && per_simd > 2 ? 2.1 : (double)p);
         const double cost = waves * (rows + 0.5) + 1.5 * (double)((p - 1) / per_simd);
         if (rows == 24 || cost < best_cost) {

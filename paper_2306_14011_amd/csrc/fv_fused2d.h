@@ -537,7 +537,7 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
     const int nwaves = (gridDim.x * blockDim.x) >> 6;
     const int wave0 = __builtin_amdgcn_readfirstlane(
         (int)((xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 6));
-    if (STAGE == 1 && blockIdx.x == 0) lam_clear(lam, ngrids, threadIdx.x, blockDim.x);  // stage 1 has read it
+    if (STAGE == 1 && blockIdx.x == 0) lam_clear_of(lam, grids, ngrids, threadIdx.x, blockDim.x);  // stage 1 has read it
     for (int item = wave0; item < nitems; item += nwaves) {
         unsigned long long t_start = 0;
         if (clk) t_start = wall_clock64();

@@ -92,6 +92,13 @@ __device__ __forceinline__ void lam_clear(unsigned long long* lam, int ngrids, i
     for (int i = t; i < 2 * ngrids * LAM_SLOTS; i += nt) lam[i * LAM_PAD] = 0ull;
 }
 
+// The same for the ngrids grids of a table.
+__device__ __forceinline__ void lam_clear_of(unsigned long long* lam, const FGrid* __restrict__ grids, int ngrids, int t,
+                                             int nt) {
+    for (int i = t; i < 2 * ngrids * LAM_SLOTS; i += nt)
+        lam[lam_index(grids[i / (2 * LAM_SLOTS)].gid, i % (2 * LAM_SLOTS))] = 0ull;
+}
+
 // Buffer access with a wave-uniform descriptor (the grid's array), a per-lane
 // 32-bit byte offset (the column) and a wave-uniform 32-bit byte offset (the
 // variable and row): no per-lane 64-bit address arithmetic.

@@ -26,9 +26,9 @@ __host__ __device__ inline int clk_index(int entry, int slot) { return (entry * 
 // needs no clearing launch of its own.
 constexpr int LAM_SLOTS = 32;
 constexpr int LAM_PAD = 32;  // unsigned long longs per slot (256 bytes)
-__host__ __device__ inline int lam_index(int grid, int slot) { return (grid * LAM_SLOTS + slot) * LAM_PAD; }
+__host__ __device__ inline int lam_index(int grid, int slot) { return (2 * grid * LAM_SLOTS + slot) * LAM_PAD; }
 inline size_t lam_bytes(int ngrids) { return (size_t)2 * ngrids * LAM_SLOTS * LAM_PAD * 8; }
-inline unsigned long long* lam_first(unsigned long long* lam, int ngrids) { return lam + lam_index(ngrids, 0); }
+inline unsigned long long* lam_first(unsigned long long* lam) { return lam + lam_index(0, LAM_SLOTS); }
 
 // (FGridHead: what the kernels keep in scalar registers.)
 struct FGridHead {
@@ -100,7 +100,7 @@ int fused3d_slots();
 int fused3d_init_items(const FGrid3& G);
 int fused3d_auto_seg(const FGrid3& G, int cus);
 int fused_auto_seg(const FGrid* grids, int ngrids, int slots);
-int fused_rows(const FGrid& G, int seg, int cus, int per_simd);
+int fused_rows(const FGrid* grids, int ngrids, int seg, int cus, int per_simd);
 
 // whole 2D steps in one launch each (fv_step2d.hip); cus: the device's compute units. ws: step2d_bytes() of
 // scratch; step: the step's number in the call; launch_step2d_init: the first

@@ -45,3 +45,35 @@ def test_own_split_of_the_rows(n, kind):
         assert np.allclose(dts, rdt, rtol=1e-13, atol=0)
         for v in range(4):
             assert np.abs(own[v] - ref[v]).max() <= 1e-11 * np.abs(ref[v]).max(), v
+
+
+@pytest.mark.parametrize("kind", ["periodic", "viscous"])
+@pytest.mark.parametrize("sizes", [[(64, 31), (61, 130)], [(200, 150), (333, 77), (128, 256), (90, 301)],
+                                   [(700, 500), (400, 640), (1000, 333)],
+                                   # more than one round of resident waves: advanced in groups
+                                   [(1000, 900), (64, 31), (1000, 901), (600, 1500), (1000, 900), (1020, 910)]],
+                         ids=["2", "4", "3", "groups"])
+def test_own_split_of_a_batch(sizes, kind):
+    from paper_2306_14011_amd import fv
+    specs, states = zip(*[spec_of(kind, *n) for n in sizes])
+    import torch
+    outs = []
+    for segs in (None, "timed", [4 * (3 + q) for q in range(len(sizes))], [24] * len(sizes)):
+        B = fv.Batch(specs)
+        if segs == "timed":
+            B.set_timing(5)
+            segs = None
+        if segs:
+            B.set_schedule(segs)
+        reported, _, nitems = B.info()
+        assert all(s % 4 == 0 for s in reported) and (segs is None or reported == segs)
+        if segs:
+            assert nitems == sum(-(-n[0] // 60) * -(-n[1] // s) for n, s in zip(sizes, segs))
+        for q, U in enumerate(states):
+            B.view(q).copy_(torch.as_tensor(np.ascontiguousarray(U)).view(B.view(q).shape))
+        B.step(3)
+        B.step(2)
+        outs.append([B.view(q).cpu().numpy() for q in range(len(sizes))] + [B.dt()])
+        B.close()
+    for other in outs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(outs[0], other))
