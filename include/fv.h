@@ -274,9 +274,9 @@ int fv_clear_status(fv_ctx* ctx);
  * tile of the plane over a segment of planes, one workgroup of four
  * wavefronts); `waves` is the
  * number of wavefronts launched (0 = one per work item, else a grid-stride
- * loop over the items). In 2D a height equal to the library's choice stands
- * for the library's own split, which may cut the rows a little differently
- * (and not in fours). Every segment height and wave count gives bitwise the
+ * loop over the items). A height equal to the library's choice (with waves
+ * = 0) stands for the library's own split, which may cut the rows or planes a
+ * little differently (and not in fours). Every segment height and wave count gives bitwise the
  * same result. Both paths compute the same cell arithmetic; fv_residual always
  * uses the split kernels, and fv_adjoint_step recomputes its stage states with
  * the fused stage kernels of the current table (the library's choice until a

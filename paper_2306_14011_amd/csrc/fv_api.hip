@@ -649,10 +649,10 @@ static int set_fused_stage(fv_ctx* c, int st, int32_t seg, int32_t waves) {
         memcpy(G.q, c->bcs.q, sizeof(G.q));
         c->fauto[st] = fvk::fused3d_auto_seg(G, c->cus);
         if (seg == 0) seg = c->fauto[st];
-        G.seg = seg;
+        G.seg = seg == c->fauto[st] && waves == 0 ? fvk::fused3d_planes(G, seg, c->cus) : seg;
         e = hipMemcpyAsync(c->fgrid[st], &G, sizeof(G), hipMemcpyHostToDevice, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        c->fitems[st] = fvk::fused3d_items(G, seg);
+        c->fitems[st] = fvk::fused3d_items(G, G.seg);
         c->finit = fvk::fused3d_init_items(G);
     } else {
         fvk::FGrid G;

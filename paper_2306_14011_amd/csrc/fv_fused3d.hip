@@ -4,7 +4,7 @@
 // combination, and the last stage also the CFL max of the new state.
 //
 // Work decomposition: a work item is a tile of TX x TY (32 x 7) cells of the (x, y)
-// plane over a segment of seg planes along z (seg a multiple of 4), and one
+// plane over a segment of seg planes along z, and one
 // workgroup of 256 threads (four wavefronts) owns an item. Thread t < TX*TY
 // owns the cell (t % TX, t / TX) of the tile and marches along z: its cell of
 // the plane and the next two, one limited slope per plane and the left state
@@ -558,26 +558,42 @@ int fused3d_slots() {
     return bmin * cus;
 }
 
-// Segment height (a multiple of 4) by the work of the busiest compute unit:
-// the items it gets, times their planes and one more for the four planes and
-// the z flux that an item starts with. An item alone on its compute unit
-// takes 1.4 times as long per plane (97x61x45 channel: 7.4 us a plane and step
-// alone, 5.3 with two or more). Among heights within 1 % the tallest, which
-// reads the fewest halo planes. The model puts 256^3 at 52 planes (measured:
-// 1680 us a step at 52, 1691 at 16, 1735 at 32, 1742 at 8, 1892 at 4) and
-// 130x120x110 at 8 (258 us; 283 at 4, 299 at 16 and at the 24 planes that
+// Work of the busiest compute unit with items of seg planes: the items it gets,
+// times their planes and one more for the four planes and the z flux that an
+// item starts with. An item alone on its compute unit takes 1.4 times as long
+// per plane (97x61x45 channel: 7.4 us a plane and step alone, 5.3 with two or
+// more).
+static double busiest_cu(const FGrid3& G, int seg, int cus) {
+    const long long per_cu = (fused3d_items(G, seg) + cus - 1) / cus;
+    return (double)per_cu * (seg + 1) * (per_cu == 1 ? 1.4 : 1.0);
+}
+
+// Segment height (a multiple of 4) of the least such work, among heights within
+// 1 % the tallest, which reads the fewest halo planes: 52 planes at 256^3
+// (measured: 1680 us a step at 52, 1691 at 16, 1735 at 32, 1742 at 8, 1892 at
+// 4), 8 at 130x120x110 (258 us; 283 at 4, 299 at 16 and at the 24 planes that
 // counting rounds of two workgroups per compute unit gave).
 int fused3d_auto_seg(const FGrid3& G, int cus) {
     if (cus <= 0) return 16;
-    auto cost = [&](int seg) {
-        const long long per_cu = (fused3d_items(G, seg) + cus - 1) / cus;
-        return (double)per_cu * (seg + 1) * (per_cu == 1 ? 1.4 : 1.0);
-    };
+    auto cost = [&](int seg) { return busiest_cu(G, seg, cus); };
     double least = cost(4);
     for (int seg = 8; seg <= 256; seg += 4) least = fmin(least, cost(seg));
     int seg = 256;
     while (seg > 4 && cost(seg) > 1.01 * least) seg -= 4;
     return seg;
+}
+
+// Planes per item that a grid is split into where the height is the library's:
+// up to three items a compute unit, any height of less work for the busiest
+// one. A step at heights in fours and by this rule: 24^3 41.3 and 21.3 us (one
+// plane), 40^3 44.4 and 29.1 (one), 64^3 59.0 and 51.0 (three), 200x33x90 98
+// and 89 (seven). Larger grids gain less than the halo planes cost.
+int fused3d_planes(const FGrid3& G, int seg, int cus) {
+    if (cus <= 0 || fused3d_items(G, seg) > 3LL * cus) return seg;
+    int best = seg;
+    for (int planes = seg + 3; planes >= 1; --planes)
+        if (busiest_cu(G, planes, cus) < busiest_cu(G, best, cus)) best = planes;
+    return best;
 }
 
 }  // namespace fvk

@@ -99,6 +99,7 @@ void launch_fused3d_init(const FGrid3* grid, int nitems, const double* U, unsign
 int fused3d_slots();
 int fused3d_init_items(const FGrid3& G);
 int fused3d_auto_seg(const FGrid3& G, int cus);
+int fused3d_planes(const FGrid3& G, int seg, int cus);
 int fused_auto_seg(const FGrid* grids, int ngrids, int slots);
 int fused_rows(const FGrid* grids, int ngrids, int seg, int cus, int per_simd);
 
