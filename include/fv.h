@@ -364,7 +364,8 @@ int fv_batch_query(int32_t ngrids, const fv_grid_desc* grids, int64_t* offsets, 
  * [4, 1024], or 0 for the library's choice over all grids of the batch
  * (fv_batch_set_schedule sets one per grid); waves: wavefronts per stage
  * launch (0 = one per work item, else a grid-stride loop); order: FV_ORDER_*
- * of the grids in the work list. With seg = 0 and waves = 0 the library also
+ * of the grids in the work list. With the library's choice for every grid
+ * (given as 0 or as the height it reports) and waves = 0 the library also
  * splits the rows its own way and may advance the batch in groups of grids,
  * all steps of one before the next; results are the same bits. The workspace
  * (queried size, 256-byte aligned) is owned by the caller. */

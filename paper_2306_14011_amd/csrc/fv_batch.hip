@@ -1,7 +1,8 @@
 // C ABI of the batched fused step: many uneven 2D grids advanced together by
 // three fused stage launches per step, captured once in a HIP graph (a
 // one-step graph and a graph of GRAPH_STEPS steps, so that a long run pays one
-// graph launch per GRAPH_STEPS steps).
+// graph launch per GRAPH_STEPS steps). A batch of several rounds of resident
+// waves is advanced in groups of grids instead (apply_schedule).
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -146,7 +147,8 @@ int validate_batch(int32_t ngrids, const fv_grid_desc* grids, BLayout* L, char* 
 
 struct fv_batch {
     int ngrids, waves, nitems, order;
-    bool own;  // the heights are the library's
+    int auto_seg;  // the library's height
+    bool own;      // every grid has it, and no wave count is given
     // Parts of the table that are advanced one after the other (one unless own).
     struct Group {
         int first, ngrids, nitems;
@@ -385,8 +387,9 @@ int fv_batch_create(int32_t ngrids, const fv_grid_desc* grids, int32_t seg, int3
                 if ((d.bc[a][sd] == FV_BC_WALL || d.bc[a][sd] == FV_BC_INFLOW) && b->mode < 1) b->mode = 1;
         if (d.mu > 0.0) b->mode = 2;
     }
-    b->own = seg == 0 && waves == 0;
-    if (seg == 0) seg = fvk::fused_auto_seg(b->by_grid.data(), ngrids, fvk::fused_slots());
+    b->auto_seg = fvk::fused_auto_seg(b->by_grid.data(), ngrids, fvk::fused_slots());
+    if (seg == 0) seg = b->auto_seg;
+    b->own = seg == b->auto_seg && waves == 0;
     for (int g = 0; g < ngrids; ++g) b->by_grid[g].seg = seg;
     hipError_t e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
     if (e != hipSuccess) {
@@ -496,7 +499,7 @@ int fv_batch_set_schedule(fv_batch* b, const int32_t* segs, int32_t order) {
             if (!valid_seg(segs[g])) return bfail(b, FV_EINVAL, "seg must be a multiple of 4 in [4, 1024]");
     if (segs) {
         for (int g = 0; g < b->ngrids; ++g) b->by_grid[g].seg = segs[g];
-        b->own = false;
+        b->own = b->waves == 0 && std::all_of(segs, segs + b->ngrids, [&](int32_t s) { return s == b->auto_seg; });
     }
     return apply_schedule(b, order);
 }

@@ -22,14 +22,16 @@
 // What bounds it: at 256^3 the last two stages fetch 2.2 and 1.8 GB and write
 // 0.7 GB in 0.5 and 0.57 ms, above the rate of a large copy (4.8 TB/s; part of
 // the halo cells comes from the caches); the first two keep the FP64 units
-// 57 % busy, and the
-// rest is the latency of the plane loads between two barriers, which is why
-// the loads of the next plane are issued as soon as their registers are free
-// and the first two stages are held to 168 registers (three workgroups per
-// CU). 256^3: 1.68 ms a step (1.57 with rows on whole lines), against 1.79 with a window of four planes in
-// registers and two limited slopes per z face; 97x61x45 channel: 72 us,
-// against 104. Tiles of 32 x 15, 32 x 23 and 64 x 7 cells take 1.79, 1.83 and
-// 1.76 ms at 256^3, and non-temporal stores, or loads of U^n, 5 % more.
+// 57 % busy, and the rest is the latency of the plane loads between two
+// barriers, which is why the loads of the next plane are issued as soon as
+// their registers are free and the first two stages are held to 168 registers
+// (three workgroups per CU). 256^3: 1.57 ms a step, of which the rows on whole
+// lines gave 0.11, against 1.79 with a window of four planes in registers and
+// two limited slopes per z face; 97x61x45 channel: 68 us, against 104. Tiles
+// of 32 x 15, 32 x 23 and 64 x 7 cells took 1.79, 1.83 and 1.76 ms where this
+// one took 1.68, non-temporal stores, or loads of U^n, 4-5 % more, and halo
+// loads two or three planes ahead, with the owned cells' planes, the same or
+// up to 5 % more.
 //
 // Halo cells outside the grid are read through the boundary maps; the state
 // may keep ghost layers but they are not read. Per-grid dt and the CFL max

@@ -70,14 +70,14 @@ def fused_step_bytes(spec):
 #   MUSCL per cell and axis: 4 variables x (the backward difference D[i] and
 #     the two face states U[i] +- minmod(D[i], D[i+1]) / 2)
 #   Roe flux per face (2D, returned as 2F): primitive states, Roe averages,
-#     wave strengths and dissipation, central fluxes; each 1/x is 6 flops and
+#     acoustic part and dissipation, central fluxes; each 1/x is 6 flops and
 #     each 1/sqrt(x) 8 (hardware estimate plus one third-order correction),
-#     3 of the latter and 1 of the former
+#     2 of the latter and 1 of the former
 #   cell update: residual of 4 faces x 4 variables (5 flops each) and the RK
 #     combination (2, 5, 5 flops in stages 1, 2, 3), averaged over the stages
 #   CFL wave speed of a cell: 1/rho, velocities, pressure, c, sum over axes
 FLOPS_MUSCL_CELL_AXIS = 4 * 5
-FLOPS_ROE_FACE_2D = 131
+FLOPS_ROE_FACE_2D = 113
 FLOPS_CELL_UPDATE_2D = 4 * (5 + 4)
 FLOPS_CELL_LAMBDA = 31
 

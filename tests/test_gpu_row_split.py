@@ -58,7 +58,7 @@ def test_own_split_of_a_batch(sizes, kind):
     specs, states = zip(*[spec_of(kind, *n) for n in sizes])
     import torch
     outs = []
-    for segs in (None, "timed", [4 * (3 + q) for q in range(len(sizes))], [24] * len(sizes)):
+    for segs in (None, "timed", [4 * (3 + q) for q in range(len(sizes))], [28] * len(sizes)):
         B = fv.Batch(specs)
         if segs == "timed":
             B.set_timing(5)
