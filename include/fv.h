@@ -473,7 +473,8 @@ int fv_mlp_predict(const float* params, int32_t n_in, const float* X, int32_t n,
  * the number of epochs done. Training stops early once the epoch loss has
  * failed to improve on the best so far by hp->tol for more than
  * hp->n_iter_no_change consecutive epochs. A launch of up to eight workgroups
- * does all the work and exchanges gradients in the workspace. */
+ * (one on a stream restricted to some of the CUs) does all the work and
+ * exchanges gradients in the workspace. */
 int fv_mlp_train(float* params, int32_t n_in, float* adam_m, float* adam_v, int32_t* adam_t, const float* X,
                  const float* y, int32_t n, const int32_t* order, const fv_mlp_hparams* hp, float* epoch_loss,
                  int32_t* epochs_run, void* workspace, size_t ws_bytes, void* stream);

@@ -415,12 +415,24 @@ __global__ void __launch_bounds__(TT) k_loss_grad(const float* __restrict__ P, c
 // each to a CU of its own, go through the same minibatches, and none waits for
 // anything but the others' counts. Rank r goes to XCD r, so that 32 launches
 // are resident whole before one could be in part, and hardware queues are
-// fewer.
+// fewer. A stream that may not use every CU of the device, and a device of
+// fewer than 64, take one workgroup.
 constexpr int MAX_WGS = 8;
 constexpr int WG_ROWS = 64;
 
-inline int train_workgroups(int batch) {
+static int train_workgroups(int batch, hipStream_t stream) {
     const int w = (batch + WG_ROWS - 1) / WG_ROWS;
+    if (w < 2) return 1;
+    int dev = 0, cus = 0, usable = 0;
+    uint32_t mask[32] = {};
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipExtStreamGetCUMask(stream, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return 1;
+    }
+    for (uint32_t m : mask) usable += __builtin_popcount(m);
+    if (cus < 64 || usable < cus) return 1;
     return w < MAX_WGS ? w : MAX_WGS;
 }
 
@@ -1104,7 +1116,7 @@ int fv_mlp_train(float* params, int32_t n_in, float* adam_m, float* adam_v, int3
         return FV_EINVAL;
     const int bmax = hp->batch < n ? hp->batch : n;
     if (ws_bytes < mlp::scratch_bytes(bmax)) return FV_EWORKSPACE;
-    const int wgs = mlp::train_workgroups(bmax);
+    const int wgs = mlp::train_workgroups(bmax, (hipStream_t)stream);
     char* const ex = (char*)(((uintptr_t)workspace + 63) & ~(uintptr_t)63);
     if (wgs > 1) hipLaunchKernelGGL(mlp::k_train_clear, dim3(1), dim3(64), 0, (hipStream_t)stream, (unsigned*)ex);
     if (n_in == FV_MLP_IN)
