@@ -92,9 +92,15 @@ __device__ __forceinline__ void lam_clear(unsigned long long* lam, int ngrids, i
     for (int i = t; i < 2 * ngrids * LAM_SLOTS; i += nt) lam[i * LAM_PAD] = 0ull;
 }
 
-// The same for the ngrids grids of a table.
+// The same for the ngrids grids of a table. (One grid's index comes with its
+// table entry: loaded by the threads, it held the first workgroup up for 2 us
+// of a step.)
 __device__ __forceinline__ void lam_clear_of(unsigned long long* lam, const FGrid* __restrict__ grids, int ngrids, int t,
                                              int nt) {
+    if (ngrids == 1) {
+        lam_clear(lam + lam_index(grids->gid, 0), 1, t, nt);
+        return;
+    }
     for (int i = t; i < 2 * ngrids * LAM_SLOTS; i += nt)
         lam[lam_index(grids[i / (2 * LAM_SLOTS)].gid, i % (2 * LAM_SLOTS))] = 0ull;
 }
