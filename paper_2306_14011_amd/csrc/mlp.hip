@@ -459,6 +459,13 @@ struct Exchange {
         while ((int)(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - count) < 0)
             __builtin_amdgcn_s_sleep(1);
     }
+    // Before a barrier after which one thread tells the other workgroups that all
+    // waves' sums are written, or read: a wave counts only its own outstanding
+    // accesses, and the barrier waits for none, so each waits for its own here.
+    // The one thread's write-back and count then come after all of them. (The
+    // fence in every thread would do too, with eight write-backs of the L2: see
+    // above.)
+    __device__ static void settle() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
     // Sums g over the workgroups, in the order of their ranks, in all of them.
     __device__ void sum(Grads& g) {
         unsigned* const ctr = (unsigned*)base;
@@ -476,6 +483,7 @@ struct Exchange {
             *(v4f*)(out + 4 * EX_ROW + TT / 2 * 16) = v4f{g.b1, g.b2, g.b3, g.w4};
             *(float2*)(base + EX_HEAD + rank * EX_BYTES + 4 * EX_ROW + TT * 16 + tid * 8) = float2{g.b4, g.sq};
         }
+        settle();
         __syncthreads();
         sent += size;
         taken += size;
@@ -505,6 +513,7 @@ struct Exchange {
                 g.sq += c.y;
             }
         }
+        settle();
         __syncthreads();
         if (tid == 0) __hip_atomic_fetch_add(ctr + 32, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
     }
