@@ -474,10 +474,25 @@ int fv_mlp_predict(const float* params, int32_t n_in, const float* X, int32_t n,
  * failed to improve on the best so far by hp->tol for more than
  * hp->n_iter_no_change consecutive epochs. A launch of up to eight workgroups
  * (one on a stream restricted to some of the CUs) does all the work and
- * exchanges gradients in the workspace. */
+ * exchanges gradients in the workspace; where they cannot all be resident at
+ * once (a graph replayed on a restricted stream, a device full of other work)
+ * one computes all shares, with the same bits. The workspace belongs to
+ * the call until it has completed: another call that uses it meanwhile breaks
+ * the exchange. Every wait is bounded; a call that loses one ends with
+ * *epochs_run = -1 and leaves params, the moments and adam_t as they were. */
 int fv_mlp_train(float* params, int32_t n_in, float* adam_m, float* adam_v, int32_t* adam_t, const float* X,
                  const float* y, int32_t n, const int32_t* order, const fv_mlp_hparams* hp, float* epoch_loss,
                  int32_t* epochs_run, void* workspace, size_t ws_bytes, void* stream);
+
+/* fv_mlp_train with the bounds of its workgroups' waits given, in polls of
+ * about 0.14 microseconds (>= 0): roll_polls until all have arrived (0: one
+ * computes all shares), wait_polls for each other's gradients (0: the first
+ * wait is lost). A single workgroup waits for nothing. For tests and for
+ * callers with bounds of their own. */
+int fv_mlp_train_bounded(float* params, int32_t n_in, float* adam_m, float* adam_v, int32_t* adam_t, const float* X,
+                         const float* y, int32_t n, const int32_t* order, const fv_mlp_hparams* hp, float* epoch_loss,
+                         int32_t* epochs_run, void* workspace, size_t ws_bytes, int32_t roll_polls, int32_t wait_polls,
+                         void* stream);
 
 /* Search space of launch vectors: site s has radix[s] choices (1 = pinned);
  * choice c gives parameters (p1[s][c], p2[s][c]) and the network features

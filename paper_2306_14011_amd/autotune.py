@@ -133,6 +133,8 @@ class Network:
                         X.data_ptr(), y.data_ptr(), n, order_t.data_ptr(), hpc, losses.data_ptr(), ne.data_ptr(),
                         ws.data_ptr(), ws_bytes, self._stream())
         nrun = int(ne.item())
+        if nrun < 0:
+            raise RuntimeError("fv_mlp_train: the workgroups lost each other; the network is as it was")
         return losses.cpu().numpy()[:nrun]
 
     def loss_grad(self, X, y, alpha):

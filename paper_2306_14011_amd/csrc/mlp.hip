@@ -97,6 +97,7 @@ struct alignas(16) TrainLds {
     float b4;
     float y[CROWS], part[2][CROWS], dout[CROWS];
     float red[TT / 64];
+    unsigned verdict, lost;  // the exchange's, from thread 0 to all
 };
 
 // Sums of a minibatch that a lane owns: tiles of the weight gradients (result
@@ -411,11 +412,19 @@ __global__ void __launch_bounds__(TT) k_loss_grad(const float* __restrict__ P, c
 // place of one cost 2.4 us more, and 64 rows then took 13.0 us on one and 16.8
 // on two. All workgroups on one XCD take 1 us less, but would queue the
 // trainings of several streams on its 32 CUs.)
-// The waits end: a launch's at most eight workgroups are dispatched in order,
-// each to a CU of its own, go through the same minibatches, and none waits for
-// anything but the others' counts. Rank r goes to XCD r, so that 32 launches
-// are resident whole before one could be in part, and hardware queues are
-// fewer. A stream that may not use every CU of the device, and a device of
+// A workgroup waits for others only once all of a launch are known to be
+// resident: they may not be (other launches or processes hold CUs, or a graph
+// that was captured here is replayed on a stream of fewer CUs), and one that
+// waits for another that its own CU would have to run never ends. So a launch
+// begins with a roll call: whoever arrives last makes it TOGETHER, and whoever
+// has waited long enough makes it STAND_ALONE, in which all leave and a launch
+// of one workgroup behind it computes every rank's share, one after another.
+// Both give the same bits.
+// Resident workgroups stay so, which ends the later waits; they are bounded too
+// (a second call on the same scratch breaks them), and a call that loses one
+// reports it and leaves the network as it was.
+// Rank r goes to XCD r, so that 32 launches are resident whole before one could
+// be in part. A stream that may not use every CU of the device, and a device of
 // fewer than 64, take one workgroup.
 constexpr int MAX_WGS = 8;
 constexpr int WG_ROWS = 64;
@@ -436,10 +445,19 @@ static int train_workgroups(int batch, hipStream_t stream) {
     return w < MAX_WGS ? w : MAX_WGS;
 }
 
-// Exchange buffer, in the caller's scratch (from a multiple of 64 bytes on): two
-// counters, then per workgroup its sums of a minibatch as every lane holds
-// them: four vectors of four, and for the lanes of the first four waves two
-// more and two values.
+// Polls of a counter (0.14 us each) before a wait is given up: some 40 ms for
+// the roll call, which no launch that finds the CUs free needs, and 5 s between
+// resident workgroups, which take microseconds. They count the time that the
+// workgroup runs, so a process that is set aside loses nothing.
+constexpr int ROLL_POLLS = 1 << 18;
+constexpr int WAIT_POLLS = 1 << 25;
+
+// Exchange buffer, in the caller's scratch (from a multiple of 64 bytes on): four
+// words in lines of their own, then per workgroup its sums of a minibatch as
+// every lane holds them: four vectors of four, and for the lanes of the first
+// four waves two more and two values.
+enum { EX_SENT = 0, EX_ARRIVED = 16, EX_TAKEN = 32, EX_VERDICT = 48 };
+enum { TOGETHER = 1, STAND_ALONE = 2 };
 constexpr size_t EX_HEAD = 256;
 constexpr size_t EX_ROW = TT * 16;                                // bytes of a vector of every lane
 constexpr size_t EX_BYTES = 4 * EX_ROW + TT / 2 * (16 + 16 + 8);  // 43008 per workgroup
@@ -453,11 +471,40 @@ static_assert(exchange_fits(), "the scratch of the smallest batch for a number o
 struct Exchange {
     char* base;
     int rank, size;
+    int polls;       // the bound of a wait between resident workgroups
     unsigned sent, taken;  // what the counters reach when all have written, and have read, a minibatch's sums
 
-    __device__ static void wait(unsigned* ctr, unsigned count) {
-        while ((int)(__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - count) < 0)
+    __device__ unsigned* word(int at) const { return (unsigned*)base + at; }
+    // Whether the counter reached count within the bound.
+    __device__ bool wait(int at, unsigned count) const {
+        for (int i = 0; i < polls; ++i) {
+            if ((int)(__hip_atomic_load(word(at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - count) >= 0) return true;
             __builtin_amdgcn_s_sleep(1);
+        }
+        return false;
+    }
+    // Thread 0: says that this workgroup is resident (with bound 0: none is called).
+    __device__ void arrive(int bound) const {
+        if (bound > 0 && __hip_atomic_fetch_add(word(EX_ARRIVED), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
+                             (unsigned)size)
+            decide(TOGETHER);
+    }
+    // The first verdict of the launch stands.
+    __device__ unsigned decide(unsigned verdict) const {
+        unsigned first = 0;
+        return __hip_atomic_compare_exchange_strong(word(EX_VERDICT), &first, verdict, __ATOMIC_RELAXED,
+                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                   ? verdict
+                   : first;
+    }
+    // Thread 0: the verdict, which all workgroups see alike.
+    __device__ unsigned roll_call(int bound) const {
+        for (int i = 0; i < bound; ++i) {
+            const unsigned v = __hip_atomic_load(word(EX_VERDICT), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (v != 0) return v;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        return decide(STAND_ALONE);
     }
     // Before a barrier after which one thread tells the other workgroups that all
     // waves' sums are written, or read: a wave counts only its own outstanding
@@ -466,33 +513,25 @@ struct Exchange {
     // fence in every thread would do too, with eight write-backs of the L2: see
     // above.)
     __device__ static void settle() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-    // Sums g over the workgroups, in the order of their ranks, in all of them.
-    __device__ void sum(Grads& g) {
-        unsigned* const ctr = (unsigned*)base;
+
+    // Writes g as the sums of rank r.
+    __device__ void put(const Grads& g, int r) const {
         const int tid = threadIdx.x;
-        const bool first4 = tid < TT / 2;  // uniform over a wave
-        char* const out = base + EX_HEAD + rank * EX_BYTES + tid * 16;
-        if (tid == 0) wait(ctr + 32, taken);  // every workgroup has read the previous minibatch's sums
-        __syncthreads();
+        char* const out = base + EX_HEAD + r * EX_BYTES + tid * 16;
         *(v4f*)out = g.w3[0];
         *(v4f*)(out + EX_ROW) = g.w3[1];
         *(v4f*)(out + 2 * EX_ROW) = g.w2[0];
         *(v4f*)(out + 3 * EX_ROW) = g.w2[1];
-        if (first4) {
+        if (tid < TT / 2) {  // uniform over a wave
             *(v4f*)(out + 4 * EX_ROW) = g.w1;
             *(v4f*)(out + 4 * EX_ROW + TT / 2 * 16) = v4f{g.b1, g.b2, g.b3, g.w4};
-            *(float2*)(base + EX_HEAD + rank * EX_BYTES + 4 * EX_ROW + TT * 16 + tid * 8) = float2{g.b4, g.sq};
+            *(float2*)(base + EX_HEAD + r * EX_BYTES + 4 * EX_ROW + TT * 16 + tid * 8) = float2{g.b4, g.sq};
         }
-        settle();
-        __syncthreads();
-        sent += size;
-        taken += size;
-        if (tid == 0) {
-            __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-            wait(ctr, sent);
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        }
-        __syncthreads();
+    }
+    // g: the sums of all ranks, in their order (every lane reads what its like wrote).
+    __device__ void take(Grads& g) const {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));  // addresses formed anew at each call, as in each_owned (in put it cost 1.5 us a minibatch)
         g.clear();
 #pragma unroll 1
         for (int r = 0; r < size; ++r) {
@@ -501,7 +540,7 @@ struct Exchange {
             g.w3[1] += *(const v4f*)(in + EX_ROW);
             g.w2[0] += *(const v4f*)(in + 2 * EX_ROW);
             g.w2[1] += *(const v4f*)(in + 3 * EX_ROW);
-            if (first4) {
+            if (tid < TT / 2) {
                 g.w1 += *(const v4f*)(in + 4 * EX_ROW);
                 const v4f b = *(const v4f*)(in + 4 * EX_ROW + TT / 2 * 16);
                 g.b1 += b[0];
@@ -513,26 +552,55 @@ struct Exchange {
                 g.sq += c.y;
             }
         }
+    }
+    // Sums g over the workgroups, in all of them; false (in every thread): a wait was given up.
+    __device__ bool sum(TrainLds& S, Grads& g) {
+        const bool first = threadIdx.x == 0;
+        // every workgroup has read the previous minibatch's sums
+        if (first && !wait(EX_TAKEN, taken)) S.lost = 1;
+        __syncthreads();
+        put(g, rank);
         settle();
         __syncthreads();
-        if (tid == 0) __hip_atomic_fetch_add(ctr + 32, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        sent += size;
+        taken += size;
+        if (first) {
+            __hip_atomic_fetch_add(word(EX_SENT), 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            if (!wait(EX_SENT, sent)) S.lost = 1;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        __syncthreads();
+        take(g);
+        const int lost = __builtin_amdgcn_readfirstlane((int)S.lost);
+        settle();
+        __syncthreads();
+        if (first) __hip_atomic_fetch_add(word(EX_TAKEN), 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        return lost == 0;
     }
 };
 
 // Clears the counters (a kernel, so that the call can be captured in a graph).
 __global__ void k_train_clear(unsigned* ctr) { ctr[threadIdx.x] = 0; }
 
-template <int IN>
+// ALONE: the launch of one workgroup that follows a shared one and computes
+// the shares of all its `size` ranks, one after another, where the roll call
+// says so; else it ends at once. (In one kernel with the shared path, which
+// fills the registers, that path took 0.4 to 1.5 us more a minibatch; the second
+// launch takes 2 us of a call.)
+template <int IN, bool ALONE>
 __global__ void __launch_bounds__(TT) k_train(float* P, float* M, float* V, int32_t* tptr, const float* __restrict__ X,
                                               const float* __restrict__ Y, int n, const int32_t* __restrict__ order,
-                                              fv_mlp_hparams hp, float* epoch_loss, int32_t* epochs_run, char* exchange) {
+                                              fv_mlp_hparams hp, float* epoch_loss, int32_t* epochs_run, char* exchange,
+                                              int size, int roll_polls, int wait_polls) {
     __shared__ TrainLds S;
-    const int rank = blockIdx.x, size = gridDim.x;
+    const int rank = ALONE ? 0 : blockIdx.x;
+    Exchange ex{exchange, rank, size, wait_polls, 0, 0};
+    if (ALONE && *ex.word(EX_VERDICT) != STAND_ALONE) return;
     if (hp.max_epochs <= 0) {
         if (rank == 0 && threadIdx.x == 0) *epochs_run = 0;
         return;
     }
-    Exchange ex{exchange, rank, size, 0, 0};
+    if (!ALONE && size > 1 && threadIdx.x == 0) ex.arrive(roll_polls);
     int t = *tptr;
     // running powers of the decay factors for the bias correction
     double p1 = pow((double)hp.beta1, (double)t), p2 = pow((double)hp.beta2, (double)t);
@@ -544,40 +612,60 @@ __global__ void __launch_bounds__(TT) k_train(float* P, float* M, float* V, int3
         m[k] = M[at];
         v[k] = V[at];
     });
+    if (!ALONE && size > 1) {
+        if (threadIdx.x == 0) {
+            S.verdict = ex.roll_call(roll_polls);
+            S.lost = 0;
+        }
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane((int)S.verdict) != TOGETHER) return;
+    }
     float best = FLT_MAX;
     int noimp = 0;
     int e = 0;
-    // This workgroup's rows of a minibatch of sz rows: part of them, from lo.
-    auto lo = [&](int sz) { return (int)((long long)sz * rank / size); };
-    auto part = [&](int sz) { return (int)((long long)sz * (rank + 1) / size) - lo(sz); };
+    // Rank r's rows of a minibatch of sz rows: part of them, from lo.
+    auto lo = [&](int sz, int r) { return (int)((long long)sz * r / size); };
+    auto part = [&](int sz, int r) { return (int)((long long)sz * (r + 1) / size) - lo(sz, r); };
     RowFetch<IN> next;
     {
         const int sz = min(hp.batch, n);
-        next.load(X, Y, order, lo(sz), part(sz));
+        next.load(X, Y, order, lo(sz, rank), part(sz, rank));
     }
     for (; e < hp.max_epochs; ++e) {
         float acc = 0.f;  // this lane's part of the epoch's loss
         const int32_t* rows = order + (size_t)e * n;
         for (int start = 0; start < n; start += hp.batch) {
-            const int sz = min(hp.batch, n - start), own = part(sz);
+            const int sz = min(hp.batch, n - start);
             const float inv = 1.0f / (float)sz;
-            g.clear();
-            for (int c = 0; c == 0 || c < own; c += CROWS) {
-                next.store(S);
-                __syncthreads();
-                // the following chunk: of this minibatch, of the next one, or of the next epoch
-                if (c + CROWS < own) {
-                    next.load(X, Y, rows, start + lo(sz) + c + CROWS, own - c - CROWS);
-                } else if (start + sz < n) {
-                    const int nsz = min(hp.batch, n - start - sz);
-                    next.load(X, Y, rows, start + sz + lo(nsz), part(nsz));
-                } else if (e + 1 < hp.max_epochs) {
-                    const int nsz = min(hp.batch, n);
-                    next.load(X, Y, rows + n, lo(nsz), part(nsz));
+            int r = rank;
+            do {
+                const int own = part(sz, r);
+                g.clear();
+                for (int c = 0; c == 0 || c < own; c += CROWS) {
+                    next.store(S);
+                    __syncthreads();
+                    // the following chunk: of this share, of the next one, of the next minibatch, or of the next epoch
+                    if (c + CROWS < own) {
+                        next.load(X, Y, rows, start + lo(sz, r) + c + CROWS, own - c - CROWS);
+                    } else if (ALONE && r + 1 < size) {
+                        next.load(X, Y, rows, start + lo(sz, r + 1), part(sz, r + 1));
+                    } else if (start + sz < n) {
+                        const int nsz = min(hp.batch, n - start - sz);
+                        next.load(X, Y, rows, start + sz + lo(nsz, rank), part(nsz, rank));
+                    } else if (e + 1 < hp.max_epochs) {
+                        const int nsz = min(hp.batch, n);
+                        next.load(X, Y, rows + n, lo(nsz, rank), part(nsz, rank));
+                    }
+                    train_chunk(S, min(CROWS, own - c), inv, g);
                 }
-                train_chunk(S, min(CROWS, own - c), inv, g);
+                if (ALONE) ex.put(g, r);
+            } while (ALONE && ++r < size);
+            if (ALONE) {
+                ex.take(g);
+            } else if (size > 1 && !ex.sum(S, g)) {
+                if (rank == 0 && threadIdx.x == 0) *epochs_run = -1;
+                return;
             }
-            if (size > 1) ex.sum(g);
             ++t;
             p1 *= (double)hp.beta1;
             p2 *= (double)hp.beta2;
@@ -1112,11 +1200,12 @@ int fv_mlp_predict(const float* params, int32_t n_in, const float* X, int32_t n,
     return mlp_check_launch();
 }
 
-int fv_mlp_train(float* params, int32_t n_in, float* adam_m, float* adam_v, int32_t* adam_t, const float* X,
-                 const float* y, int32_t n, const int32_t* order, const fv_mlp_hparams* hp, float* epoch_loss,
-                 int32_t* epochs_run, void* workspace, size_t ws_bytes, void* stream) {
+int fv_mlp_train_bounded(float* params, int32_t n_in, float* adam_m, float* adam_v, int32_t* adam_t, const float* X,
+                         const float* y, int32_t n, const int32_t* order, const fv_mlp_hparams* hp, float* epoch_loss,
+                         int32_t* epochs_run, void* workspace, size_t ws_bytes, int32_t roll_polls, int32_t wait_polls,
+                         void* stream) {
     if (!params || !adam_m || !adam_v || !adam_t || !X || !y || !order || !hp || !epoch_loss || !epochs_run ||
-        !workspace)
+        !workspace || roll_polls < 0 || wait_polls < 0)
         return FV_EINVAL;
     if (n_in != FV_MLP_IN && n_in != FV_MLP_IN_SIZED) return FV_EINVAL;
     if (n < 1 || n > mlp::MAXN || hp->batch < 1 || hp->max_epochs < 0 || hp->n_iter_no_change < 0) return FV_EINVAL;
@@ -1128,13 +1217,26 @@ int fv_mlp_train(float* params, int32_t n_in, float* adam_m, float* adam_v, int3
     const int wgs = mlp::train_workgroups(bmax, (hipStream_t)stream);
     char* const ex = (char*)(((uintptr_t)workspace + 63) & ~(uintptr_t)63);
     if (wgs > 1) hipLaunchKernelGGL(mlp::k_train_clear, dim3(1), dim3(64), 0, (hipStream_t)stream, (unsigned*)ex);
-    if (n_in == FV_MLP_IN)
-        hipLaunchKernelGGL(mlp::k_train<FV_MLP_IN>, dim3(wgs), dim3(mlp::TT), 0, (hipStream_t)stream, params, adam_m,
-                           adam_v, adam_t, X, y, n, order, *hp, epoch_loss, epochs_run, ex);
-    else
-        hipLaunchKernelGGL(mlp::k_train<FV_MLP_IN_SIZED>, dim3(wgs), dim3(mlp::TT), 0, (hipStream_t)stream, params,
-                           adam_m, adam_v, adam_t, X, y, n, order, *hp, epoch_loss, epochs_run, ex);
+#define FV_TRAIN(IN, ALONE, GRID)                                                                                 \
+    hipLaunchKernelGGL((mlp::k_train<IN, ALONE>), dim3(GRID), dim3(mlp::TT), 0, (hipStream_t)stream, params,       \
+                       adam_m, adam_v, adam_t, X, y, n, order, *hp, epoch_loss, epochs_run, ex, wgs, roll_polls, \
+                       wait_polls)
+    if (n_in == FV_MLP_IN) {
+        FV_TRAIN(FV_MLP_IN, false, wgs);
+        if (wgs > 1) FV_TRAIN(FV_MLP_IN, true, 1);
+    } else {
+        FV_TRAIN(FV_MLP_IN_SIZED, false, wgs);
+        if (wgs > 1) FV_TRAIN(FV_MLP_IN_SIZED, true, 1);
+    }
+#undef FV_TRAIN
     return mlp_check_launch();
+}
+
+int fv_mlp_train(float* params, int32_t n_in, float* adam_m, float* adam_v, int32_t* adam_t, const float* X,
+                 const float* y, int32_t n, const int32_t* order, const fv_mlp_hparams* hp, float* epoch_loss,
+                 int32_t* epochs_run, void* workspace, size_t ws_bytes, void* stream) {
+    return fv_mlp_train_bounded(params, n_in, adam_m, adam_v, adam_t, X, y, n, order, hp, epoch_loss, epochs_run,
+                                workspace, ws_bytes, mlp::ROLL_POLLS, mlp::WAIT_POLLS, stream);
 }
 
 int fv_mlp_sweep_workspace(size_t* bytes) {

@@ -204,6 +204,7 @@ def lib():
         L.fv_mlp_predict.argtypes = [_vp, ctypes.c_int32, _vp, ctypes.c_int32, _vp, _vp]
         L.fv_mlp_train.argtypes = [_vp, ctypes.c_int32, _vp, _vp, _vp, _vp, _vp, ctypes.c_int32, _vp,
                                    ctypes.POINTER(fv_mlp_hparams), _vp, _vp, _vp, ctypes.c_size_t, _vp]
+        L.fv_mlp_train_bounded.argtypes = L.fv_mlp_train.argtypes[:-1] + [ctypes.c_int32, ctypes.c_int32, _vp]
         L.fv_mlp_sweep.argtypes = [_vp, ctypes.POINTER(fv_tune_space), ctypes.c_int64, ctypes.c_int64,
                                    ctypes.c_int32, _vp, _vp, _vp, ctypes.c_size_t, _vp]
         L.fv_mlp_sweep_static.argtypes = [_vp, ctypes.POINTER(fv_tune_space), ctypes.c_int64, ctypes.c_int64,
@@ -214,7 +215,8 @@ def lib():
                      "fv_get_fused_launch", "fv_fused_slots", "fv_batch_query", "fv_batch_create",
                      "fv_batch_step", "fv_batch_set_timing", "fv_batch_dt", "fv_batch_status", "fv_batch_info", "fv_batch_set_schedule", "fv_batch_destroy",
                      "fv_mlp_workspace", "fv_mlp_sweep_workspace",
-                     "fv_mlp_loss_grad", "fv_mlp_predict", "fv_mlp_train", "fv_mlp_sweep", "fv_mlp_sweep_static"):
+                     "fv_mlp_loss_grad", "fv_mlp_predict", "fv_mlp_train", "fv_mlp_train_bounded", "fv_mlp_sweep",
+                     "fv_mlp_sweep_static"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -499,6 +501,15 @@ def fv_mlp_train(params_ptr, n_in, m_ptr, v_ptr, t_ptr, X_ptr, y_ptr, n, order_p
                                          _vp(X_ptr), _vp(y_ptr), int(n), _vp(order_ptr), ctypes.byref(hp),
                                          _vp(loss_ptr), _vp(epochs_ptr), _vp(ws_ptr), ws_bytes, _vp(stream_ptr)),
                       "fv_mlp_train")
+
+
+def fv_mlp_train_bounded(params_ptr, n_in, m_ptr, v_ptr, t_ptr, X_ptr, y_ptr, n, order_ptr, hp, loss_ptr, epochs_ptr,
+                         ws_ptr, ws_bytes, roll_polls, wait_polls, stream_ptr):
+    return _mlp_check(lib().fv_mlp_train_bounded(_vp(params_ptr), int(n_in), _vp(m_ptr), _vp(v_ptr), _vp(t_ptr),
+                                                 _vp(X_ptr), _vp(y_ptr), int(n), _vp(order_ptr), ctypes.byref(hp),
+                                                 _vp(loss_ptr), _vp(epochs_ptr), _vp(ws_ptr), ws_bytes,
+                                                 int(roll_polls), int(wait_polls), _vp(stream_ptr)),
+                      "fv_mlp_train_bounded")
 
 
 def fv_mlp_sweep(params_ptr, space, begin, count, k, top_idx_ptr, top_val_ptr, ws_ptr, ws_bytes, stream_ptr):

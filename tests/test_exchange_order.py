@@ -23,7 +23,7 @@ pytestmark = pytest.mark.skipif(not os.path.exists(LIB) or not all(os.path.exist
 
 @pytest.fixture(scope="module")
 def train_kernels(tmp_path_factory):
-    """Instructions of the training kernels, by name."""
+    """Instructions of the shared training kernels, by name."""
     d = tmp_path_factory.mktemp("codeobj")
     fat = d / "fatbin"
     subprocess.run([TOOLS[0], f"--dump-section=.hip_fatbin={fat}", LIB, str(d / "lib.so")], check=True,
@@ -41,7 +41,7 @@ def train_kernels(tmp_path_factory):
         text = subprocess.run([OBJDUMP, "-d", str(co)], check=True, capture_output=True, text=True).stdout
         for block in re.split(r"^[0-9a-f]+ <", text, flags=re.M)[1:]:
             name, _, body = block.partition(">:")
-            if re.search(r"k_trainILi\d+E", name):
+            if re.search(r"k_trainILi\d+ELb0E", name):
                 out[name] = [line.split("//")[0].strip() for line in body.splitlines() if line.strip()]
     shutil.rmtree(d, ignore_errors=True)
     return out
