@@ -50,6 +50,7 @@ size_t a256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct BLayout {
     std::vector<int64_t> offsets;
+    int slots;  // wave-speed slots of all grids
     size_t off_fgrid, off_lam, off_dt, off_status, off_clk, off_counter, off_U1, off_U2, total;
 };
 
@@ -126,7 +127,9 @@ int validate_batch(int32_t ngrids, const fv_grid_desc* grids, BLayout* L, char* 
     L->off_fgrid = o;
     o = a256(o + sizeof(fvk::FGrid) * ngrids);
     L->off_lam = o;
-    o = a256(o + fvk::lam_bytes(ngrids));
+    L->slots = 0;
+    for (int g = 0; g < ngrids; ++g) L->slots += fvk::lam_slots(grids[g].n[0] * grids[g].n[1]);
+    o = a256(o + fvk::lam_bytes(L->slots));
     L->off_dt = o;
     o = a256(o + 8 * (size_t)ngrids);
     L->off_status = o;
@@ -147,6 +150,7 @@ int validate_batch(int32_t ngrids, const fv_grid_desc* grids, BLayout* L, char* 
 
 struct fv_batch {
     int ngrids, waves, nitems, order;
+    int slots;     // wave-speed slots of all grids
     int auto_seg;  // the library's height
     bool own;      // every grid has it, and no wave count is given
     // Parts of the table that are advanced one after the other (one unless own).
@@ -345,6 +349,8 @@ int fv_batch_create(int32_t ngrids, const fv_grid_desc* grids, int32_t seg, int3
     b->U2 = (double*)(base + L.off_U2);
     // table entries by grid; each keeps the element offset of its own slot of the state
     b->by_grid.resize(ngrids);
+    b->slots = L.slots;
+    int slot = 0;
     for (int g = 0; g < ngrids; ++g) {
         const fv_grid_desc& d = grids[g];
         fvk::FGrid& G = b->by_grid[g];
@@ -359,6 +365,10 @@ int fv_batch_create(int32_t ngrids, const fv_grid_desc* grids, int32_t seg, int3
         G.bcy0 = d.bc[1][0];
         G.bcy1 = d.bc[1][1];
         G.gid = g;
+        G.lam0 = slot;
+        const int slots = fvk::lam_slots(d.n[0] * d.n[1]);
+        G.lmask = G.lclear = slots - 1;
+        slot += slots;
         G.base = L.offsets[g];
         G.sv = (long long)G.nx * G.ny;
         const double dx = (d.hi[0] - d.lo[0]) / (double)d.n[0];
@@ -416,7 +426,7 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps) {
     const bool timed = b->history != nullptr;
     if (b->groups.size() > 1 && !timed) {
         // launches of a full round each: no graph needed to hide them
-        fvk::launch_lam_reset(b->lam, b->ngrids, b->stream);
+        fvk::launch_lam_reset(b->lam, b->slots, b->stream);
         for (const fv_batch::Group& q : b->groups) {
             fvk::launch_fused_init(b->grids + q.first, q.ngrids, q.nitems, U, b->lam, b->status, b->stream);
             for (int32_t s = 0; s < nsteps; ++s) enqueue_stages(b, q, U, nullptr, b->stream);
@@ -446,7 +456,7 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps) {
         b->graph_timed = timed;
         b->graph_history = b->history;
     }
-    fvk::launch_lam_reset(b->lam, b->ngrids, b->stream);
+    fvk::launch_lam_reset(b->lam, b->slots, b->stream);
     for (const fv_batch::Group& q : b->groups)
         fvk::launch_fused_init(b->grids + q.first, q.ngrids, q.nitems, U, b->lam, b->status, b->stream);
     for (int32_t s = 0; s < nsteps;) {

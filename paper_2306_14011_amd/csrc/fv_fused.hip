@@ -63,14 +63,15 @@ __global__ void __launch_bounds__(256) k_fused_lambda(const FGrid* __restrict__ 
     lmax = wave_max_d(lmax);
     fl = wave_or(fl);
     if (lane == 0) {
-        lam_add(lam, G.gid, item, lmax);
+        lam_add(lam, G.lam0, G.lmask, item, lmax);
         if (fl) atomicOr(status, fl);
     }
 }
 
 // Zero the lambda accumulators.
-__global__ void k_lam_reset(unsigned long long* lam, int ngrids) {
-    lam_clear(lam, ngrids, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+__global__ void k_lam_reset(unsigned long long* lam, int slots) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < slots) lam[i * LAM_PAD] = 0ull;
 }
 
 // ---------------------------------------------------------------------------
@@ -105,9 +106,8 @@ void launch_fused_stage(int stage, int waves, const FGrid* grids, int ngrids, in
 #undef FV_LFS
 }
 
-void launch_lam_reset(unsigned long long* lam, int ngrids, hipStream_t s) {
-    const int n = 2 * ngrids * LAM_SLOTS;
-    hipLaunchKernelGGL(k_lam_reset, dim3((n + 255) / 256), dim3(256), 0, s, lam, ngrids);
+void launch_lam_reset(unsigned long long* lam, int slots, hipStream_t s) {
+    hipLaunchKernelGGL(k_lam_reset, dim3((slots + 255) / 256), dim3(256), 0, s, lam, slots);
 }
 
 // lam: cleared slots.

@@ -23,7 +23,7 @@
 // the previous step's stage 3 (or the init kernel) accumulated; stage 2
 // resets the accumulator; stage 3 accumulates lambda_max(U^{n+1}) with an
 // atomic max on the bit pattern of the (non-negative) double, spread over the
-// grid's slots (lam_index).
+// grid's slots.
 //
 // The kernel template lives in this header so that the curvilinear variant
 // can be instantiated in a source of its own, built with multiply-add
@@ -537,7 +537,6 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
     const int nwaves = (gridDim.x * blockDim.x) >> 6;
     const int wave0 = __builtin_amdgcn_readfirstlane(
         (int)((xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 6));
-    if (STAGE == 1 && blockIdx.x == 0) lam_clear_of(lam, grids, ngrids, threadIdx.x, blockDim.x);  // stage 1 has read it
     for (int item = wave0; item < nitems; item += nwaves) {
         unsigned long long t_start = 0;
         if (clk) t_start = wall_clock64();
@@ -547,9 +546,10 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
         const int local = item - G.work0;
         const int strip = local % G.strips;
         const int sidx = local / G.strips;
+        if (STAGE == 1 && local == 0) lam_clear(lam, grids[gi].lam0, grids[gi].lclear, lane);  // stage 1 has read it
         double dt;
         if (STAGE == 0) {
-            dt = dt_fixed ? dt_fixed[G.gid] : G.cfl / lam_read(lam, G.gid, lane);
+            dt = dt_fixed ? dt_fixed[G.gid] : G.cfl / lam_read(lam, grids[gi].lam0, grids[gi].lmask, lane);
             if (local == 0 && lane == 0) {
                 dtg[G.gid] = dt;
                 if (dt_out) dt_out[G.gid] = dt;
@@ -577,7 +577,7 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
             lmax = wave_max_d(lmax);
             fl = wave_or(fl);
             if (lane == 0) {
-                lam_add(lam, G.gid, item, lmax);
+                lam_add(lam, grids[gi].lam0, grids[gi].lmask, item, lmax);
                 if (fl) atomicOr(status, fl);
             }
         }
