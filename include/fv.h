@@ -366,7 +366,7 @@ int fv_batch_query(int32_t ngrids, const fv_grid_desc* grids, int64_t* offsets, 
  * launch (0 = one per work item, else a grid-stride loop); order: FV_ORDER_*
  * of the grids in the work list. With the library's choice for every grid
  * (given as 0 or as the height it reports) and waves = 0 the library also
- * splits the rows its own way and may advance the batch in groups of grids,
+ * splits the rows its own way and may advance a batch of large grids in groups,
  * all steps of one before the next; results are the same bits. The workspace
  * (queried size, 256-byte aligned) is owned by the caller. */
 int fv_batch_create(int32_t ngrids, const fv_grid_desc* grids, int32_t seg, int32_t waves, int32_t order,
@@ -374,7 +374,9 @@ int fv_batch_create(int32_t ngrids, const fv_grid_desc* grids, int32_t seg, int3
 
 /* Advances every grid of the batch state U (device) by nsteps steps, each
  * grid with its own CFL dt. The steps are replayed from HIP graphs captured
- * at the first call for U (one of 8 steps, one of 1 step for the rest). */
+ * at the first call for U (one of 8 steps, one of 1 step for the rest), or,
+ * where the library advances the batch in groups (fv_batch_create), launched
+ * one stage and group at a time. */
 int fv_batch_step(fv_batch* b, double* U, int32_t nsteps);
 
 /* Device-clock record of each step: when history (device, max_steps *
@@ -382,7 +384,9 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps);
  * writes, per grid and stage, the earliest work-item start and the latest
  * work-item end (wall_clock64 ticks) to history[((n * ngrids + g) * 3 + stage) * 2 + {0,1}]
  * for n < max_steps. NULL turns recording off. *ticks_per_us receives the
- * clock rate. */
+ * clock rate. While it is on, every stage is one launch over all grids: a batch
+ * that is otherwise advanced in groups runs another schedule then (with the
+ * same bits). */
 int fv_batch_set_timing(fv_batch* b, uint64_t* history, int32_t max_steps, double* ticks_per_us);
 
 /* Copies the dt of the last step of every grid to dt (device, ngrids doubles). */

@@ -2,7 +2,7 @@
 // three fused stage launches per step, captured once in a HIP graph (a
 // one-step graph and a graph of GRAPH_STEPS steps, so that a long run pays one
 // graph launch per GRAPH_STEPS steps). A batch of several rounds of resident
-// waves is advanced in groups of grids instead (apply_schedule).
+// waves of large grids is advanced in groups of grids instead (apply_schedule).
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -125,7 +125,7 @@ int validate_batch(int32_t ngrids, const fv_grid_desc* grids, BLayout* L, char* 
     const size_t total_el = (size_t)L->offsets[ngrids];
     size_t o = 0;
     L->off_fgrid = o;
-    o = a256(o + sizeof(fvk::FGrid) * ngrids);
+    o = a256(o + 2 * sizeof(fvk::FGrid) * ngrids);
     L->off_lam = o;
     L->slots = 0;
     for (int g = 0; g < ngrids; ++g) L->slots += fvk::lam_slots(grids[g].n[0] * grids[g].n[1]);
@@ -153,11 +153,13 @@ struct fv_batch {
     int slots;     // wave-speed slots of all grids
     int auto_seg;  // the library's height
     bool own;      // every grid has it, and no wave count is given
-    // Parts of the table that are advanced one after the other (one unless own).
+    // Parts of the table: the whole batch, then the groups, if there are more than
+    // one, that a call of group_steps steps or more advances one after the other.
     struct Group {
         int first, ngrids, nitems;
     };
     std::vector<Group> groups;
+    int group_steps;
     int mode;  // stage-kernel variant: 0 periodic / transmissive, 1 walls or inflow faces, 2 viscous
     hipStream_t stream, cap;
     fvk::FGrid* grids;
@@ -202,6 +204,11 @@ static void drop_graph(fv_batch* b) {
     b->graph_history = nullptr;
 }
 
+// Enqueues the wave speeds of U's grids of group q into cleared slots.
+static void enqueue_init(fv_batch* b, const fv_batch::Group& q, const double* U) {
+    fvk::launch_fused_init(b->grids + q.first, q.ngrids, q.nitems, U, b->lam, b->status, b->stream);
+}
+
 // Enqueues the three stages of a step of the grids of group q.
 static void enqueue_stages(fv_batch* b, const fv_batch::Group& q, double* U, unsigned long long* clk, hipStream_t s) {
     const fvk::FGrid* grids = b->grids + q.first;
@@ -218,7 +225,7 @@ static void enqueue_step(fv_batch* b, double* U, hipStream_t s) {
     const int nclk = 6 * b->ngrids;
     unsigned long long* clk = b->history ? b->clk : nullptr;
     if (clk) hipLaunchKernelGGL(k_clk_reset, dim3(1), dim3(256), 0, s, b->clk, nclk);
-    for (const fv_batch::Group& q : b->groups) enqueue_stages(b, q, U, clk, s);
+    enqueue_stages(b, b->groups[0], U, clk, s);
     if (clk) hipLaunchKernelGGL(k_clk_store, dim3(1), dim3(256), 0, s, b->clk, nclk, b->history, b->max_steps, b->counter);
 }
 
@@ -227,13 +234,16 @@ static bool valid_seg(int32_t seg) { return seg >= 4 && seg <= 1024 && seg % 4 =
 // Splits the grids into the least number of groups that 24-row items of each
 // fill the device's resident waves (cap) at most once, evenly: the largest
 // grid left goes to the group with the least work. part[g]: the group of grid g.
-static int split_groups(const std::vector<fvk::FGrid>& grids, long long cap, std::vector<int>& part) {
+// Grids of fewer than 20 items on average (some 150 cells a side) stay together.
+// steps: the steps of a call from which on groups pay (apply_schedule).
+static int split_groups(const std::vector<fvk::FGrid>& grids, long long cap, std::vector<int>& part, int& steps) {
     const int n = (int)grids.size();
     part.assign(n, 0);
     auto items = [&](int g) { return (long long)fvk::fused_items(grids[g], 24); };
     long long total = 0;
     for (int g = 0; g < n; ++g) total += items(g);
-    if (cap <= 0 || total <= cap) return 1;
+    if (cap <= 0 || total <= cap || total < 20LL * n) return 1;
+    steps = total < 48LL * n ? 4 : 1;
     std::vector<int> perm(n);
     std::iota(perm.begin(), perm.end(), 0);
     std::stable_sort(perm.begin(), perm.end(), [&](int a, int c) { return items(a) > items(c); });
@@ -247,17 +257,24 @@ static int split_groups(const std::vector<fvk::FGrid>& grids, long long cap, std
     return k;
 }
 
-// Orders the table by group and work-list order, assigns each grid its segment
-// height and first work item (counted within its group), and uploads it. Work
-// items of a grid are contiguous; the step's graph is rebuilt on the next step.
+// Orders the table by work-list order, assigns each grid its segment height and
+// first work item, and uploads it; the step's graph is rebuilt on the next step.
 //
-// With the heights at the library's choice, a batch of more than one round of
-// resident waves is advanced in groups of one round each, all steps of a group
-// before the next: the waves of a round march in step, so that the halo rows
-// they share are still in L2, and a group's states stay in the last-level
-// cache from stage to stage. 96 grids of 128 to 1024 cells a side (30M cells),
-// 8 steps: 14.3 ms in one group, 13.2 in eight of one round each, 13.7 in
-// seven, 13.5 in ten.
+// With the heights at the library's choice, a second table holds the grids in
+// groups of one round of resident waves each (split_groups), each with rows of
+// its own and its work items counted from 0. A call advances a group by all its
+// steps before the next: the waves of a round march in step, so that the halo
+// rows they share are still in L2, and a group's states stay in the last-level
+// cache from stage to stage and from step to step. That pays for large grids,
+// for middling ones in calls of some steps, and not for small ones, which share
+// few halo rows and lose at the ends of more launches. us a step, one launch for
+// all and in groups, calls of 16, 4 and 1 steps: 96 grids of 128 to 1024 cells a
+// side (30M cells) 1700 / 1740 / 1880 and 1580 / 1630 / 1850; 96 of 256^2
+// 383 / 388 / 409 and 372 / 380 / 428; 224 of 192^2 505 / 513 / 550 and
+// 495 / 513 / 573; 320 of 160^2 482 / 490 / 528 and 483 / 498 / 560; 512 of 128^2
+// 583 / 591 / 615 and 576 / 588 / 662; 2048 of 64^2 642 / 646 / 695 and
+// 670 / 662 / 735; 8192 of 32^2 655 / 666 / 705 and 731 / 764 / 853; 65536 of 8^2
+// 1036 / 1062 / 1139 and 1356 / 1432 / 1732.
 static int apply_schedule(fv_batch* b, int32_t order) {
     const int n = b->ngrids;
     std::vector<int> perm(n);
@@ -267,40 +284,41 @@ static int apply_schedule(fv_batch* b, int32_t order) {
             return (long long)b->by_grid[a].nx * b->by_grid[a].ny > (long long)b->by_grid[c].nx * b->by_grid[c].ny;
         });
     std::vector<int> part(n, 0);
-    int k = 1, cus = 0;
+    int k = 1, cus = 0, steps = 1;
     const int per_simd = b->mode == 2 ? 2 : 3;  // resident waves
     if (b->own) {
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             cus = 0;
-        k = split_groups(b->by_grid, 4LL * cus * per_simd, part);
+        k = split_groups(b->by_grid, 4LL * cus * per_simd, part, steps);
     }
     std::vector<fvk::FGrid> table;
     std::vector<fv_batch::Group> groups;
-    long long work = 0;
-    for (int q = 0; q < k; ++q) {
+    // the whole batch, then the groups
+    for (int q = k > 1 ? -1 : 0; q < k; ++q) {
+        const bool all = groups.empty();
         const int first = (int)table.size();
         for (int g : perm)
-            if (part[g] == q) table.push_back(b->by_grid[g]);
+            if (all || part[g] == q) table.push_back(b->by_grid[g]);
         fvk::FGrid* grids = table.data() + first;
         const int count = (int)table.size() - first;
         const int rows = b->own ? fvk::fused_rows(grids, count, grids[0].seg, cus, per_simd) : 0;
-        long long own = 0;
+        long long work = 0;
         for (int i = 0; i < count; ++i) {
             if (rows) grids[i].seg = rows;
-            grids[i].work0 = (int)own;
-            own += fvk::fused_items(grids[i], grids[i].seg);
+            grids[i].work0 = (int)work;
+            work += fvk::fused_items(grids[i], grids[i].seg);
         }
-        work += own;
         if (work > 0x7fffffff) return bfail(b, FV_EINVAL, "too many work items");
-        groups.push_back({first, count, (int)own});
+        groups.push_back({first, count, (int)work});
     }
     b->host_grids.swap(table);
     b->groups.swap(groups);
-    b->nitems = (int)work;
+    b->group_steps = steps;
+    b->nitems = b->groups[0].nitems;
     b->order = order;
-    hipError_t e = hipMemcpyAsync(b->grids, b->host_grids.data(), sizeof(fvk::FGrid) * n, hipMemcpyHostToDevice,
+    hipError_t e = hipMemcpyAsync(b->grids, b->host_grids.data(), sizeof(fvk::FGrid) * b->host_grids.size(), hipMemcpyHostToDevice,
                                   b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) return bfail(b, FV_EDEVICE, "grid table upload failed");
@@ -424,12 +442,12 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps) {
     if (!U || nsteps < 0) return bfail(b, FV_EINVAL, "null state or negative step count");
     if (nsteps == 0) return FV_OK;
     const bool timed = b->history != nullptr;
-    if (b->groups.size() > 1 && !timed) {
+    if (b->groups.size() > 1 && !timed && nsteps >= b->group_steps) {
         // launches of a full round each: no graph needed to hide them
         fvk::launch_lam_reset(b->lam, b->slots, b->stream);
-        for (const fv_batch::Group& q : b->groups) {
-            fvk::launch_fused_init(b->grids + q.first, q.ngrids, q.nitems, U, b->lam, b->status, b->stream);
-            for (int32_t s = 0; s < nsteps; ++s) enqueue_stages(b, q, U, nullptr, b->stream);
+        for (size_t q = 1; q < b->groups.size(); ++q) {
+            enqueue_init(b, b->groups[q], U);
+            for (int32_t s = 0; s < nsteps; ++s) enqueue_stages(b, b->groups[q], U, nullptr, b->stream);
         }
         const hipError_t e = hipGetLastError();
         return e == hipSuccess ? FV_OK : bfail(b, FV_EDEVICE, hipGetErrorString(e));
@@ -457,8 +475,7 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps) {
         b->graph_history = b->history;
     }
     fvk::launch_lam_reset(b->lam, b->slots, b->stream);
-    for (const fv_batch::Group& q : b->groups)
-        fvk::launch_fused_init(b->grids + q.first, q.ngrids, q.nitems, U, b->lam, b->status, b->stream);
+    enqueue_init(b, b->groups[0], U);
     for (int32_t s = 0; s < nsteps;) {
         const bool many = nsteps - s >= GRAPH_STEPS;
         hipError_t e = hipGraphLaunch(many ? b->exec_many : b->exec, b->stream);

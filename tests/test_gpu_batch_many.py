@@ -40,6 +40,32 @@ def test_many_grids_as_alone(kind):
     B.close()
 
 
+# more than one round of resident waves: middling grids (advanced in groups by
+# calls of four steps or more) and large ones (by every call)
+@pytest.mark.parametrize("shapes, n", [([(192, 191), (190, 215)], 111), ([(251, 260), (300, 310)], 61)],
+                         ids=["middling", "large"])
+@pytest.mark.parametrize("kind", ["periodic", "viscous"])
+def test_groups_of_grids_as_alone(kind, shapes, n):
+    kinds = [spec_of(kind, *s) for s in shapes]
+    alone = []
+    for g, U in kinds:
+        s = fv.Solver(g)
+        s.set_path(fv.FV_PATH_FUSED, 16)
+        s.set_state(U)
+        s.step(8)
+        alone.append(s.get_state().reshape(4, -1))
+        s.close()
+    for calls in ((8,), (1, 5, 2)):
+        B = fv.Batch([kinds[q % 2][0] for q in range(n)])
+        fill(B, [kinds[q % 2][1] for q in range(n)])
+        for steps in calls:
+            B.step(steps)
+        assert B.status()[1] == 0
+        for q in range(n):
+            assert np.array_equal(B.view(q).cpu().numpy().reshape(4, -1), alone[q % 2]), (calls, q)
+        B.close()
+
+
 @pytest.mark.parametrize("n", [1, 700, 4096])
 def test_second_stage_takes_no_longer_than_the_others(n):
     g, U = spec_of("periodic", 8, 8)
