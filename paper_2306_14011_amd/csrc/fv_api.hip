@@ -179,7 +179,7 @@ int validate(const fv_grid_desc* g, Layout* L, char* why) {
     L->off_fused = o;   // 3 x 512 B: an FGrid or FGrid3 per stage; dt at +1536
     o += 2048;
     L->off_lam = o;
-    o = align256(o + fvk::lam_bytes(2 * fvk::LAM_SLOTS));
+    o = align256(o + fvk::lam_bytes(1, fvk::LAM_SLOTS));
     L->off_step = o;
     if (nd == 2) o = align256(o + fvk::step2d_bytes());
     L->off_partial = o;
@@ -458,7 +458,7 @@ int fv_create(const fv_grid_desc* g, void* workspace, size_t workspace_bytes, vo
         c->g.met = met;
     }
     fvk::launch_set_u32(c->status, 0u, c->stream);
-    fvk::launch_lam_reset(c->flam, 2 * fvk::LAM_SLOTS, c->stream);
+    fvk::launch_lam_reset(c->flam, 1, fvk::LAM_SLOTS, c->stream);
     if (check_launch_error(c) != FV_OK) {
         snprintf(g_err, 256, "%s", c->err);
         delete c;
@@ -657,8 +657,6 @@ static int set_fused_stage(fv_ctx* c, int st, int32_t seg, int32_t waves) {
     } else {
         fvk::FGrid G;
         memset(&G, 0, sizeof(G));
-        G.lmask = fvk::LAM_SLOTS - 1;
-        G.lclear = 2 * fvk::LAM_SLOTS - 1;
         G.nx = c->g.n[0];
         G.ny = c->g.n[1];
         G.pitch = c->g.sy;

@@ -50,7 +50,7 @@ size_t a256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct BLayout {
     std::vector<int64_t> offsets;
-    int slots;  // wave-speed slots of all grids
+    int slots;  // wave-speed slots of a grid
     size_t off_fgrid, off_lam, off_dt, off_status, off_clk, off_counter, off_U1, off_U2, total;
 };
 
@@ -127,9 +127,9 @@ int validate_batch(int32_t ngrids, const fv_grid_desc* grids, BLayout* L, char* 
     L->off_fgrid = o;
     o = a256(o + 2 * sizeof(fvk::FGrid) * ngrids);
     L->off_lam = o;
-    L->slots = 0;
-    for (int g = 0; g < ngrids; ++g) L->slots += fvk::lam_slots(grids[g].n[0] * grids[g].n[1]);
-    o = a256(o + fvk::lam_bytes(L->slots));
+    L->slots = 1;
+    for (int g = 0; g < ngrids; ++g) L->slots = std::max(L->slots, fvk::lam_slots(grids[g].n[0] * grids[g].n[1]));
+    o = a256(o + fvk::lam_bytes(ngrids, L->slots));
     L->off_dt = o;
     o = a256(o + 8 * (size_t)ngrids);
     L->off_status = o;
@@ -150,7 +150,7 @@ int validate_batch(int32_t ngrids, const fv_grid_desc* grids, BLayout* L, char* 
 
 struct fv_batch {
     int ngrids, waves, nitems, order;
-    int slots;     // wave-speed slots of all grids
+    int slots;     // wave-speed slots of a grid
     int auto_seg;  // the library's height
     bool own;      // every grid has it, and no wave count is given
     // Parts of the table: the whole batch, then the groups, if there are more than
@@ -206,18 +206,19 @@ static void drop_graph(fv_batch* b) {
 
 // Enqueues the wave speeds of U's grids of group q into cleared slots.
 static void enqueue_init(fv_batch* b, const fv_batch::Group& q, const double* U) {
-    fvk::launch_fused_init(b->grids + q.first, q.ngrids, q.nitems, U, b->lam, b->status, b->stream);
+    fvk::launch_fused_init(b->grids + q.first, q.ngrids, q.nitems, U, b->lam, b->status, b->stream, nullptr,
+                           b->slots);
 }
 
 // Enqueues the three stages of a step of the grids of group q.
 static void enqueue_stages(fv_batch* b, const fv_batch::Group& q, double* U, unsigned long long* clk, hipStream_t s) {
     const fvk::FGrid* grids = b->grids + q.first;
     fvk::launch_fused_stage(0, b->waves, grids, q.ngrids, q.nitems, U, U, b->U1, b->lam, b->dt, nullptr, nullptr,
-                            b->status, clk, s, nullptr, b->mode);
+                            b->status, clk, s, nullptr, b->mode, nullptr, b->slots);
     fvk::launch_fused_stage(1, b->waves, grids, q.ngrids, q.nitems, U, b->U1, b->U2, b->lam, b->dt, nullptr, nullptr,
-                            b->status, clk, s, nullptr, b->mode);
+                            b->status, clk, s, nullptr, b->mode, nullptr, b->slots);
     fvk::launch_fused_stage(2, b->waves, grids, q.ngrids, q.nitems, U, b->U2, U, b->lam, b->dt, nullptr, nullptr,
-                            b->status, clk, s, nullptr, b->mode);
+                            b->status, clk, s, nullptr, b->mode, nullptr, b->slots);
 }
 
 // Enqueues one step (three stages, plus the clock record when timing) on s.
@@ -372,7 +373,6 @@ int fv_batch_create(int32_t ngrids, const fv_grid_desc* grids, int32_t seg, int3
     // table entries by grid; each keeps the element offset of its own slot of the state
     b->by_grid.resize(ngrids);
     b->slots = L.slots;
-    int slot = 0;
     for (int g = 0; g < ngrids; ++g) {
         const fv_grid_desc& d = grids[g];
         fvk::FGrid& G = b->by_grid[g];
@@ -387,10 +387,6 @@ int fv_batch_create(int32_t ngrids, const fv_grid_desc* grids, int32_t seg, int3
         G.bcy0 = d.bc[1][0];
         G.bcy1 = d.bc[1][1];
         G.gid = g;
-        G.lam0 = slot;
-        const int slots = fvk::lam_slots(d.n[0] * d.n[1]);
-        G.lmask = G.lclear = slots - 1;
-        slot += slots;
         G.base = L.offsets[g];
         G.sv = (long long)G.nx * G.ny;
         const double dx = (d.hi[0] - d.lo[0]) / (double)d.n[0];
@@ -448,7 +444,7 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps) {
     const bool timed = b->history != nullptr;
     if (b->groups.size() > 1 && !timed && nsteps >= b->group_steps) {
         // launches of a full round each: no graph needed to hide them
-        fvk::launch_lam_reset(b->lam, b->slots, b->stream);
+        fvk::launch_lam_reset(b->lam, b->ngrids, b->slots, b->stream);
         for (size_t q = 1; q < b->groups.size(); ++q) {
             enqueue_init(b, b->groups[q], U);
             for (int32_t s = 0; s < nsteps; ++s) enqueue_stages(b, b->groups[q], U, nullptr, b->stream);
@@ -478,7 +474,7 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps) {
         b->graph_timed = timed;
         b->graph_history = b->history;
     }
-    fvk::launch_lam_reset(b->lam, b->slots, b->stream);
+    fvk::launch_lam_reset(b->lam, b->ngrids, b->slots, b->stream);
     enqueue_init(b, b->groups[0], U);
     for (int32_t s = 0; s < nsteps;) {
         const bool many = nsteps - s >= GRAPH_STEPS;

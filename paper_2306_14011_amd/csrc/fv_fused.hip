@@ -11,7 +11,8 @@ namespace fvk {
 // the latency of its loads: four rows are read at once.
 __global__ void __launch_bounds__(256) k_fused_lambda(const FGrid* __restrict__ grids, int ngrids, int nitems,
                                                       const double* __restrict__ U, unsigned long long* __restrict__ lam,
-                                                      uint32_t* __restrict__ status, const double* __restrict__ met) {
+                                                      uint32_t* __restrict__ status, const double* __restrict__ met,
+                                                      int slots) {
     const int lane = threadIdx.x & 63;
     const int item = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
     if (item >= nitems) return;
@@ -63,7 +64,7 @@ __global__ void __launch_bounds__(256) k_fused_lambda(const FGrid* __restrict__ 
     lmax = wave_max_d(lmax);
     fl = wave_or(fl);
     if (lane == 0) {
-        lam_add(lam, G.lam0, G.lmask, item, lmax);
+        lam_add(lam, G.gid, slots, item, lmax);
         if (fl) atomicOr(status, fl);
     }
 }
@@ -86,11 +87,11 @@ int fused_strips(int nx) { return (nx + FW - 1) / FW; }
 void launch_fused_stage(int stage, int waves, const FGrid* grids, int ngrids, int nitems, const double* Un,
                         const double* Us, double* Ud, unsigned long long* lam, double* dtg, const double* dt_fixed,
                         double* dt_out, uint32_t* status, unsigned long long* clk, hipStream_t s,
-                        const double* src, int mode, const double* met) {
+                        const double* src, int mode, const double* met, int slots) {
     const dim3 grid(fused_blocks(nitems, waves)), block(256);
 #define FV_LFS(SRCB, M)                                                                                       \
     launch_fused_stage_t<SRCB, M>(stage, grid, block, grids, ngrids, nitems, Un, Us, Ud, lam, dtg, dt_fixed, \
-                                  dt_out, status, clk, src, met, s)
+                                  dt_out, status, clk, src, met, slots, s)
     if (mode == 3) {
         launch_fused_stage_curv(stage, grid, block, grids, ngrids, nitems, Un, Us, Ud, lam, dtg, dt_fixed, dt_out,
                                 status, clk, src, met, s);
@@ -106,15 +107,16 @@ void launch_fused_stage(int stage, int waves, const FGrid* grids, int ngrids, in
 #undef FV_LFS
 }
 
-void launch_lam_reset(unsigned long long* lam, int slots, hipStream_t s) {
-    hipLaunchKernelGGL(k_lam_reset, dim3((slots + 255) / 256), dim3(256), 0, s, lam, slots);
+void launch_lam_reset(unsigned long long* lam, int ngrids, int slots, hipStream_t s) {
+    const int n = 2 * ngrids * slots;
+    hipLaunchKernelGGL(k_lam_reset, dim3((n + 255) / 256), dim3(256), 0, s, lam, n);
 }
 
 // lam: cleared slots.
 void launch_fused_init(const FGrid* grids, int ngrids, int nitems, const double* U, unsigned long long* lam,
-                       uint32_t* status, hipStream_t s, const double* met) {
+                       uint32_t* status, hipStream_t s, const double* met, int slots) {
     const dim3 grid(fused_blocks(nitems, 0)), block(256);
-    hipLaunchKernelGGL(k_fused_lambda, grid, block, 0, s, grids, ngrids, nitems, U, lam, status, met);
+    hipLaunchKernelGGL(k_fused_lambda, grid, block, 0, s, grids, ngrids, nitems, U, lam, status, met, slots);
 }
 
 // Waves of the stage kernels that are resident on the current device at once:

@@ -532,7 +532,8 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
                                                  unsigned long long* __restrict__ lam, double* __restrict__ dtg,
                                                  const double* __restrict__ dt_fixed, double* __restrict__ dt_out,
                                                  uint32_t* __restrict__ status, unsigned long long* __restrict__ clk,
-                                                 const double* __restrict__ src, const double* __restrict__ met) {
+                                                 const double* __restrict__ src, const double* __restrict__ met,
+                                                 int slots) {
     const int lane = threadIdx.x & 63;
     const int nwaves = (gridDim.x * blockDim.x) >> 6;
     const int wave0 = __builtin_amdgcn_readfirstlane(
@@ -546,10 +547,9 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
         const int local = item - G.work0;
         const int strip = local % G.strips;
         const int sidx = local / G.strips;
-        if (STAGE == 1 && local == 0) lam_clear(lam, grids[gi].lam0, grids[gi].lclear, lane);  // stage 1 has read it
         double dt;
         if (STAGE == 0) {
-            dt = dt_fixed ? dt_fixed[G.gid] : G.cfl / lam_read(lam, grids[gi].lam0, grids[gi].lmask, lane);
+            dt = dt_fixed ? dt_fixed[G.gid] : G.cfl / lam_read(lam, G.gid, slots, lane);
             if (local == 0 && lane == 0) {
                 dtg[G.gid] = dt;
                 if (dt_out) dt_out[G.gid] = dt;
@@ -577,7 +577,7 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
             lmax = wave_max_d(lmax);
             fl = wave_or(fl);
             if (lane == 0) {
-                lam_add(lam, grids[gi].lam0, grids[gi].lmask, item, lmax);
+                lam_add(lam, G.gid, slots, item, lmax);
                 if (fl) atomicOr(status, fl);
             }
         }
@@ -588,6 +588,9 @@ __attribute__((amdgpu_waves_per_eu((MODE == 3 && STAGE == 0 && !SRC) ? 3 : (MODE
             atomicMax(&clk[clk_index((G.gid * 3 + STAGE) * 2 + 1, slot)], t_end);
         }
     }
+    // stage 1 has read the wave speeds, and stage 3 adds to them
+    if (STAGE == 1)
+        for (int g = wave0; g < ngrids; g += nwaves) lam_clear(lam, grids[g].gid, slots, lane);
 }
 
 static inline int fused_blocks(int nitems, int waves) {
@@ -599,16 +602,17 @@ template <bool SRC, int MODE>
 static void launch_fused_stage_t(int stage, dim3 grid, dim3 block, const FGrid* grids, int ngrids, int nitems,
                                  const double* Un, const double* Us, double* Ud, unsigned long long* lam,
                                  double* dtg, const double* dt_fixed, double* dt_out, uint32_t* status,
-                                 unsigned long long* clk, const double* src, const double* met, hipStream_t s) {
+                                 unsigned long long* clk, const double* src, const double* met, int slots,
+                                 hipStream_t s) {
     if (stage == 0)
         hipLaunchKernelGGL((k_fused2d<0, SRC, MODE>), grid, block, 0, s, grids, ngrids, nitems, Un, Us, Ud, lam, dtg,
-                           dt_fixed, dt_out, status, clk, src, met);
+                           dt_fixed, dt_out, status, clk, src, met, slots);
     else if (stage == 1)
         hipLaunchKernelGGL((k_fused2d<1, SRC, MODE>), grid, block, 0, s, grids, ngrids, nitems, Un, Us, Ud, lam, dtg,
-                           dt_fixed, dt_out, status, clk, src, met);
+                           dt_fixed, dt_out, status, clk, src, met, slots);
     else
         hipLaunchKernelGGL((k_fused2d<2, SRC, MODE>), grid, block, 0, s, grids, ngrids, nitems, Un, Us, Ud, lam, dtg,
-                           dt_fixed, dt_out, status, clk, src, met);
+                           dt_fixed, dt_out, status, clk, src, met, slots);
 }
 
 // The curvilinear variant's launches (fv_fused_curv.hip).

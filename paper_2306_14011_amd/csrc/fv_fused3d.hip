@@ -406,7 +406,7 @@ __global__ void __launch_bounds__(T3) __attribute__((amdgpu_waves_per_eu(BC || S
     const int lane = tid & 63;
     const int nblocks = gridDim.x;
     const int b0 = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x));
-    if (STAGE == 1 && blockIdx.x == 0 && tid < 64) lam_clear(lam, 0, 2 * LAM_SLOTS - 1, tid);  // stage 1 has read it
+    if (STAGE == 1 && blockIdx.x == 0 && tid < 64) lam_clear(lam, 0, LAM_SLOTS, tid);  // stage 1 has read it
     const FGrid3Head G = *grid;
     const double* gq = &grid->q[0][0][0];
     for (int item = b0; item < nitems; item += nblocks) {
@@ -414,7 +414,7 @@ __global__ void __launch_bounds__(T3) __attribute__((amdgpu_waves_per_eu(BC || S
         tile_of_item(G, item, tx0, ty0, k0);
         double dt;
         if (STAGE == 0) {
-            dt = dt_fixed ? dt_fixed[0] : G.cfl / lam_read(lam, 0, LAM_SLOTS - 1, lane);
+            dt = dt_fixed ? dt_fixed[0] : G.cfl / lam_read(lam, 0, LAM_SLOTS, lane);
             if (item == 0 && tid == 0) {
                 dtg[0] = dt;
                 if (dt_out) dt_out[0] = dt;
@@ -441,7 +441,7 @@ __global__ void __launch_bounds__(T3) __attribute__((amdgpu_waves_per_eu(BC || S
             lmax = wave_max_d(lmax);
             fl = wave_or(fl);
             if (lane == 0) {
-                lam_add(lam, 0, LAM_SLOTS - 1, 4 * item + (tid >> 6), lmax);
+                lam_add(lam, 0, LAM_SLOTS, 4 * item + (tid >> 6), lmax);
                 if (fl) atomicOr(status, fl);
             }
         }
@@ -483,7 +483,7 @@ __global__ void __launch_bounds__(T3) k_fused3d_lambda(const FGrid3* __restrict_
     lmax = wave_max_d(lmax);
     fl = wave_or(fl);
     if (lane == 0) {
-        lam_add(lam, 0, LAM_SLOTS - 1, 4 * item + (tid >> 6), lmax);
+        lam_add(lam, 0, LAM_SLOTS, 4 * item + (tid >> 6), lmax);
         if (fl) atomicOr(status, fl);
     }
 }

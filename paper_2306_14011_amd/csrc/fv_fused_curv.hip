@@ -14,10 +14,10 @@ void launch_fused_stage_curv(int stage, dim3 grid, dim3 block, const FGrid* grid
                              const double* src, const double* met, hipStream_t s) {
     if (src)
         launch_fused_stage_t<true, 3>(stage, grid, block, grids, ngrids, nitems, Un, Us, Ud, lam, dtg, dt_fixed,
-                                      dt_out, status, clk, src, met, s);
+                                      dt_out, status, clk, src, met, LAM_SLOTS, s);
     else
         launch_fused_stage_t<false, 3>(stage, grid, block, grids, ngrids, nitems, Un, Us, Ud, lam, dtg, dt_fixed,
-                                       dt_out, status, clk, src, met, s);
+                                       dt_out, status, clk, src, met, LAM_SLOTS, s);
 }
 
 }  // namespace fvk

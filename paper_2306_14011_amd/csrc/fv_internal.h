@@ -20,16 +20,17 @@ __host__ __device__ inline int clk_index(int entry, int slot) { return (entry * 
 // the other, and the waves of a stage end together (512^2: 1152 of them made
 // the last stage 23.4 us against 11.5 for the one before; over the slots it
 // takes 12). The reader takes the maximum of the slots, one per lane.
-// A single grid has two sets of LAM_SLOTS: the stage kernels accumulate in set
-// 0, the wave speed of a call's first state goes to set 1; the second stage
-// clears both, so a call needs no clearing launch of its own. A grid of a batch
-// has one set of up to LAM_SLOTS by its cells (lam_slots): its waves are few,
-// and every wave of stage 1 reads, and each step clears, all of a grid's slots.
-// 65536 grids of 8^2: 1135 us a step with 32 slots each, 1035 with one.
+// Two sets per grid: the stage kernels accumulate in set 0, the wave speed of a
+// call's first state goes to set 1; the second stage clears both, so a call
+// needs no clearing launch of its own. A grid alone has LAM_SLOTS slots a set,
+// the grids of a batch as many as the largest of them needs (lam_slots): every
+// wave of stage 1 reads, and each step clears, all of a grid's. 65536 grids of
+// 8^2: 1135 us a step with 32 slots each, 1035 with one.
 constexpr int LAM_SLOTS = 32;
 constexpr int LAM_PAD = 32;  // unsigned long longs per slot (256 bytes)
-inline size_t lam_bytes(long long slots) { return (size_t)slots * LAM_PAD * 8; }
-inline unsigned long long* lam_first(unsigned long long* lam) { return lam + LAM_SLOTS * LAM_PAD; }
+__host__ __device__ inline int lam_index(int grid, int slots, int slot) { return (2 * grid * slots + slot) * LAM_PAD; }
+inline size_t lam_bytes(int ngrids, int slots) { return (size_t)2 * ngrids * slots * LAM_PAD * 8; }
+inline unsigned long long* lam_first(unsigned long long* lam) { return lam + lam_index(0, LAM_SLOTS, LAM_SLOTS); }
 // A slot per 1024 cells, a power of two.
 inline int lam_slots(long long cells) {
     int s = 1;
@@ -40,7 +41,7 @@ inline int lam_slots(long long cells) {
 // (FGridHead: what the kernels keep in scalar registers.)
 struct FGridHead {
     int nx, ny, pitch, strips, work0, scheme;  // scheme: FV_SCHEME_*
-    int bcx0, bcx1, bcy0, bcy1, gid, seg;   // gid: the caller's grid index (dt, clocks);
+    int bcx0, bcx1, bcy0, bcy1, gid, seg;   // gid: the caller's grid index (slots of lam, dt, clocks);
                                             // seg: rows per work item (a multiple of 4)
     long long base;     // element offset of cell (0,0), variable 0
     long long sv;       // per-variable stride
@@ -50,7 +51,6 @@ struct FGridHead {
 };
 
 struct FGrid : FGridHead {
-    int lam0, lmask, lclear;    // the grid's first wave-speed slot, slots - 1, slots that a step clears - 1 (below 64)
     double q[2][2][4];  // conserved ghost state of inflow faces per axis and side (the kernels'
                         // boundary variant only: grids with slip walls or inflow faces)
 };
@@ -92,10 +92,11 @@ int fused_strips(int nx);
 void launch_fused_stage(int stage, int waves, const FGrid* grids, int ngrids, int nitems, const double* Un,
                         const double* Us, double* Ud, unsigned long long* lam, double* dtg, const double* dt_fixed,
                         double* dt_out, uint32_t* status, unsigned long long* clk, hipStream_t s,
-                        const double* src = nullptr, int mode = 0, const double* met = nullptr);
-void launch_lam_reset(unsigned long long* lam, int slots, hipStream_t s);
+                        const double* src = nullptr, int mode = 0, const double* met = nullptr,
+                        int slots = LAM_SLOTS);
+void launch_lam_reset(unsigned long long* lam, int ngrids, int slots, hipStream_t s);
 void launch_fused_init(const FGrid* grids, int ngrids, int nitems, const double* U, unsigned long long* lam,
-                       uint32_t* status, hipStream_t s, const double* met = nullptr);
+                       uint32_t* status, hipStream_t s, const double* met = nullptr, int slots = LAM_SLOTS);
 int fused_slots();
 int fused3d_items(const FGrid3& G, int seg);
 void launch_fused3d_stage(int stage, int waves, const FGrid3* grid, int nitems, const double* Un, const double* Us,

@@ -463,7 +463,7 @@ __global__ void __launch_bounds__(T) k_step2d(FGridHead G, const double* __restr
             lmax = fmax(lmax, L.lmax[w]);
             fl |= L.fl[w];
         }
-        if (lam_out) lam_add(lam_out, 0, LAM_SLOTS - 1, (int)blockIdx.x, lmax);
+        if (lam_out) lam_add(lam_out, 0, LAM_SLOTS, (int)blockIdx.x, lmax);
         if (fl) atomicOr(status, fl);
     }
 }
