@@ -35,6 +35,9 @@
  *    workspace and launch errors; no state is changed when a call returns
  *    FV_EINVAL. Non-physical states (NaN, rho <= 0, p <= 0) are recorded in a
  *    device status word read by fv_status. fv_last_error gives a message.
+ *  - Range: the flux of a face forms the product of its two densities and the
+ *    inverse of that: densities lie between 1e-153 and 1e153. A state times a
+ *    power of two in that range gives the step times that power, bit for bit.
  *  - Threading: a context is used from one host thread at a time.
  */
 #ifndef FV_H

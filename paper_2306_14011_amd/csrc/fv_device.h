@@ -224,7 +224,10 @@ __host__ __device__ __forceinline__ double sign_from(double x, double r) {
 // (102 with 4 estimates when written by wave strengths).
 //  - One root serves both densities: with y = (rL rR)^(-1/2), 1/rL = rR y^2,
 //    1/rR = rL y^2, the averaged density is rL rR y, and the Roe weight of the
-//    right state is sqrt(rR) / (sqrt(rL) + sqrt(rR)) = rR / (rR + rho~).
+//    right state is sqrt(rR) / (sqrt(rL) + sqrt(rR)) = rR / (rR + rho~). The
+//    product of the densities and its inverse have to be normal numbers: their
+//    geometric mean lies between 1e-153 and 1e153 (a root for each density took
+//    any normal one).
 //  - The dissipation is |u_n| dU plus an acoustic part. With m = min(|u_n| / c, 1)
 //    (the two acoustic speeds' half sum is max(|u_n|, c), their half difference
 //    u_n clamped to +-c), s = m with u_n's sign and t = c (1 - m):
