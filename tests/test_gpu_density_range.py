@@ -16,7 +16,7 @@ def run(g, U, path, table):
     s = fv.Solver(g)
     s.set_path(path)
     if table:
-        s.set_fused_launch([24, 24, 24], [0, 0, 0])
+        s.set_fused_launch([28, 28, 28], [0, 0, 0])
     s.set_state(U)
     dts = torch.zeros(2, dtype=torch.float64, device="cuda")
     s.step(2, dt_out=dts)
