@@ -324,11 +324,12 @@ int fv_get_path(const fv_ctx* ctx, int32_t* path, int32_t* seg, int32_t* waves);
 
 /* Per-site kernel timing, a diagnostic for profiling and the autotuner's
  * measurements. When enabled, every kernel launch of fv_step / fv_residual /
- * fv_adjoint_step is bracketed by two HIP events on the context's stream and
+ * fv_adjoint_step, but the one that finds the wave speeds of a fused call's
+ * first state, is bracketed by two HIP events on the context's stream and
  * each call waits for its last event, so enabling it serialises the host with
  * the stream; kernel durations themselves are unaffected. fv_get_timing
  * writes, per timer (FV_SITE_* and FV_TIMER_FUSED for the fused stages, or
- * the whole steps of small grids), the
+ * the whole steps of small grids and the copy after an odd number of them), the
  * accumulated milliseconds and number of launches since the last read, then
  * resets them. Either output may be NULL. */
 enum { FV_TIMER_FUSED = 7, FV_NTIMERS = 8 };

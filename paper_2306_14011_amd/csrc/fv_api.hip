@@ -577,8 +577,12 @@ static int whole_steps(fv_ctx* c, double* U, int32_t nsteps, const double* dt_in
         rc = drain_timing(c);
         if (rc != FV_OK) return rc;
     }
-    if (nsteps & 1) fvk::launch_step2d_copy(c->hgrid, c->U1, U, c->stream);
-    return check_launch_error(c);
+    if (nsteps & 1) {
+        SiteTimer t(c, FV_TIMER_FUSED);
+        fvk::launch_step2d_copy(c->hgrid, c->U1, U, c->stream);
+    }
+    const int rc = check_launch_error(c);
+    return rc == FV_OK ? drain_timing(c) : rc;
 }
 
 static int fused_step(fv_ctx* c, double* U, int32_t nsteps, const double* dt_in, double* dt_out) {
