@@ -379,7 +379,10 @@ class FusedAutotuner(Autotuner):
     step runs): the launch surface is FusedSpace, each stage's segment height
     and wave count; the reference is the library's own table (automatic
     segment height, one wave per work item). Every table gives the same bits,
-    which each sample's check confirms."""
+    which each sample's check confirms. A table of the library's own heights with
+    one wave per item stands for its own split of the rows, and on small 2D grids
+    for a whole step per launch, which no other table can ask for: the reference
+    alone is timed with them."""
 
     def make_space(self):
         from .tune_space import FusedSpace
@@ -399,8 +402,11 @@ class FusedAutotuner(Autotuner):
 class BatchAutotuner:
     """The same method applied to the schedule of a batch of 2D grids: the
     segment height per grid-size bucket and the work-list order (BatchSpace),
-    each sample timed as graph-replayed batch steps. The reference schedule is
-    the library's own choice (one automatic segment height, given order)."""
+    each sample timed as batch steps. The reference schedule is the library's own
+    choice (one automatic segment height, given order). It alone is timed with the
+    library's split of the rows and, in large batches, its groups of grids, which
+    stand for the library's heights and cannot be asked for otherwise; the samples
+    run with exactly their heights."""
 
     def __init__(self, grids, states, seed=0, steps=10, warmup=2, check_steps=1, log_path=None):
         import torch

@@ -166,16 +166,17 @@ int fused_auto_seg(const FGrid* grids, int ngrids, int slots) {
 }
 
 // Rows per item that a set of grids is split into where the height is the
-// library's:
-// fused_auto_seg counts rounds of resident waves in steps of four rows, but a
-// SIMD whose last wave arrives late finishes late, whatever the rest does. So,
-// up to grids that 24-row items fill once, the height (2 .. 24) minimises the
-// time of the busiest SIMD: its p waves, times their rows and half a row for
-// the face below, in order of arrival 1.4 for a lone wave (nothing hides its
-// latencies), 2.1 for two where three could be resident, and 1.5 for every
-// further round of residents. (per_simd: resident waves a SIMD, 3; 2 for the
-// viscous and curvilinear kernels, above 168 registers.) Measured, a step, at
-// heights in the steps of four and by this rule: 512^2 30.8 and 27.3 us,
+// library's: fused_auto_seg counts rounds of resident waves in steps of four
+// rows, but a SIMD whose last wave arrives late finishes late, whatever the rest
+// does. So, up to grids that take three 24-row items a SIMD (one round of the
+// plain kernels, one and a half of those that hold two waves a SIMD, whose grids
+// gain in their second round too: the 3328x1024 figure below), the height
+// (2 .. 24) minimises the time of the busiest SIMD: its p waves, times their rows
+// and half a row for the face below, in order of arrival 1.4 for a lone wave
+// (nothing hides its latencies), 2.1 for two where three could be resident, and
+// 1.5 for every further round of residents. (per_simd: resident waves a SIMD, 3;
+// 2 for the viscous and curvilinear kernels, above 168 registers.) Measured, a
+// step, at heights in the steps of four and by this rule: 512^2 30.8 and 27.3 us,
 // 768^2 47.6 and 43.8, 1024^2 74.7 and 68.0, 1500x1100 channel 116 and 104;
 // viscous 1024^2 94 and 80, 1500^2 165 and 144; curvilinear 768^2 75 and 64,
 // 3328x1024 329 and 309. At 2048^2 both give 24 rows.

@@ -4,7 +4,7 @@
 // the last stage also the CFL max of the new state.
 //
 // Work decomposition: a work item is a 60-column strip x seg-row segment of
-// one grid (seg a multiple of 4, per grid in the table); one wavefront (64
+// one grid (seg per grid in the table, any number of rows); one wavefront (64
 // lanes) owns an item. Lane l holds column
 // x0 + l, x0 = 60*strip - 2, so lanes 2..61 produce the 60 output columns and
 // lanes 0, 1, 62, 63 carry the x halo. The wave marches up the segment one row

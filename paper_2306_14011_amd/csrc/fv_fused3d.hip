@@ -20,12 +20,12 @@
 // plane is staged, and after the face fluxes are written.
 //
 // What bounds it: at 256^3 the last two stages fetch 2.2 and 1.8 GB and write
-// 0.7 GB in 0.5 and 0.57 ms, above the rate of a large copy (4.8 TB/s; part of
-// the halo cells comes from the caches); the first two keep the FP64 units
-// 57 % busy, and the rest is the latency of the plane loads between two
+// 0.7 GB in 0.52 and 0.59 ms (5.5 and 4.3 TB/s; a large copy reaches 4.8, part
+// of the halo cells comes from the caches); the three keep the FP64 units 62, 59
+// and 57 % busy, and the rest is the latency of the plane loads between two
 // barriers, which is why the loads of the next plane are issued as soon as
 // their registers are free and the first two stages are held to 168 registers
-// (three workgroups per CU). 256^3: 1.57 ms a step, of which the rows on whole
+// (three workgroups per CU). 256^3: 1.57 to 1.63 ms a step, of which the rows on whole
 // lines gave 0.11, against 1.79 with a window of four planes in registers and
 // two limited slopes per z face; 97x61x45 channel: 68 us, against 104. Tiles
 // of 32 x 15, 32 x 23 and 64 x 7 cells took 1.79, 1.83 and 1.76 ms where this
@@ -392,8 +392,9 @@ __device__ __forceinline__ void tile_of_item(const FGrid3Head& G, int item, int&
     k0 = (r / tiles_y) * G.seg;
 }
 
-// At least 2 waves per SIMD: the stage-3 kernel with the ghost rules and a
-// source term would take 257 registers and run at 1 wave per SIMD.
+// Three waves per SIMD (168 registers) in the first two stages without ghost
+// rules; two elsewhere: the stage-3 kernel with the ghost rules and a source term
+// would take 257 registers otherwise and run at one.
 template <int STAGE, bool SRC, bool BC>
 __global__ void __launch_bounds__(T3) __attribute__((amdgpu_waves_per_eu(BC || STAGE == 2 ? 2 : 3))) k_fused3d(const FGrid3* __restrict__ grid, int nitems, const double* Un,
                                                 const double* __restrict__ Us, double* Ud,

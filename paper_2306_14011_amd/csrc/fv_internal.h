@@ -42,7 +42,7 @@ inline int lam_slots(long long cells) {
 struct FGridHead {
     int nx, ny, pitch, strips, work0, scheme;  // scheme: FV_SCHEME_*
     int bcx0, bcx1, bcy0, bcy1, gid, seg;   // gid: the caller's grid index (slots of lam, dt, clocks);
-                                            // seg: rows per work item (a multiple of 4)
+                                            // seg: rows per work item
     long long base;     // element offset of cell (0,0), variable 0
     long long sv;       // per-variable stride
     double ax, ay;      // face areas of x faces (dy) and y faces (dx)
@@ -57,7 +57,7 @@ struct FGrid : FGridHead {
 
 // The 3D grid of the fused path (device memory, read uniformly).
 struct FGrid3Head {
-    int nx, ny, nz, strips, seg, scheme;       // seg: planes per work item (a multiple of 4)
+    int nx, ny, nz, strips, seg, scheme;       // seg: planes per work item
     int bcx0, bcx1, bcy0, bcy1, bcz0, bcz1;
     long long base;                                // element offset of cell (0,0,0), variable 0
     long long sv, py, pz;                          // strides: variable, row (y), plane (z)

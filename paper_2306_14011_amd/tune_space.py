@@ -239,7 +239,8 @@ class FusedSpace(MixedRadixSpace):
     holds (one per item, or a grid-stride loop over 1/2, 1 or 2 times the
     device's resident wave slots); sites 3-6 are pinned. 8 x 4 choices per
     stage: 32^3 = 32768 points. Features: log2 of the segment height and
-    log2 of the waves actually launched (at most one per item)."""
+    log2 of the waves actually launched (at most one per item). The point of the
+    library's heights with one wave per item is the library's own split."""
 
     def __init__(self, spec, slots: int):
         self.spec = spec
