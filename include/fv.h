@@ -388,9 +388,10 @@ int fv_batch_step(fv_batch* b, double* U, int32_t nsteps);
  * writes, per grid and stage, the earliest work-item start and the latest
  * work-item end (wall_clock64 ticks) to history[((n * ngrids + g) * 3 + stage) * 2 + {0,1}]
  * for n < max_steps. NULL turns recording off. *ticks_per_us receives the
- * clock rate. While it is on, every stage is one launch over all grids: a batch
- * that is otherwise advanced in groups runs another schedule then (with the
- * same bits). */
+ * clock rate. While it is on, steps follow one another for the whole batch: one
+ * that is otherwise advanced in groups, all steps of one before the next, takes
+ * its groups one after the other within each step then, or all grids together
+ * (with the same bits). */
 int fv_batch_set_timing(fv_batch* b, uint64_t* history, int32_t max_steps, double* ticks_per_us);
 
 /* Copies the dt of the last step of every grid to dt (device, ngrids doubles). */

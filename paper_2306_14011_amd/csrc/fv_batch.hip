@@ -221,12 +221,17 @@ static void enqueue_stages(fv_batch* b, const fv_batch::Group& q, double* U, uns
                             b->status, clk, s, nullptr, b->mode, nullptr, b->slots);
 }
 
-// Enqueues one step (three stages, plus the clock record when timing) on s.
+// Enqueues one step (three stages, plus the clock record when timing) on s. With
+// the record, a batch that every call advances in groups takes its groups one
+// after the other within the step.
 static void enqueue_step(fv_batch* b, double* U, hipStream_t s) {
     const int nclk = 6 * b->ngrids;
     unsigned long long* clk = b->history ? b->clk : nullptr;
     if (clk) hipLaunchKernelGGL(k_clk_reset, dim3(1), dim3(256), 0, s, b->clk, nclk);
-    enqueue_stages(b, b->groups[0], U, clk, s);
+    if (clk && b->groups.size() > 1 && b->group_steps == 1)
+        for (size_t q = 1; q < b->groups.size(); ++q) enqueue_stages(b, b->groups[q], U, clk, s);
+    else
+        enqueue_stages(b, b->groups[0], U, clk, s);
     if (clk) hipLaunchKernelGGL(k_clk_store, dim3(1), dim3(256), 0, s, b->clk, nclk, b->history, b->max_steps, b->counter);
 }
 
