@@ -407,8 +407,8 @@ __global__ void __launch_bounds__(TT) k_loss_grad(const float* __restrict__ P, c
 // on one workgroup, of which some 6 are matrix products, and the exchange of
 // 43 KB a workgroup through the last-level cache 4.6 us more, so that a
 // workgroup takes up to 64 rows before another is added. 200-row minibatches:
-// 33.3 us on one workgroup, 22.1 on two, 17.7 on four; 500 rows 73, 42, 26, and
-// 21.5 on eight; 128 rows 20.5, and 16.1 on two. (Fences in every thread in
+// 33.3 us on one workgroup, 22.1 on two, 17.9 on four; 500 rows 73, 42, 26, and
+// 21.2 on eight; 128 rows 20.5, and 16.4 on two. (Fences in every thread in
 // place of one cost 2.4 us more, and 64 rows then took 13.0 us on one and 16.8
 // on two. All workgroups on one XCD take 1 us less, but would queue the
 // trainings of several streams on its 32 CUs.)
