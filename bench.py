@@ -23,7 +23,7 @@ Other legs (each reported in its own field):
   tuner_seeds, sized_tuner
             the paper's tuning loop over three seeds, and the size-conditioned network
   small     64^2 vortex: fused by direct launches vs graph-replayed batch of one
-  batch     96 uneven 2D grids, fused stages in a HIP graph, schedule (segment height per
+  batch     96 uneven 2D grids, fused stages, schedule (segment height per
             grid-size bucket, work-list order) chosen by the MLP autotuner; p50/p99 per-grid step time
   adjoint   512^2 vortex, 60 steps, checkpoints every 10: adjoint / primal
   copy      device-to-device copy bandwidth of a 2 GiB buffer (reference)
@@ -564,7 +564,7 @@ def batch_leg(torch, fv, inputs, steps, samples):
         s.close()
     tune.pop("tuned")
     return {
-        "workload": "96 periodic 2D vortex grids, sides U{128..1024}, beta U[1,5], FP64, 3 fused stages per step in a HIP graph",
+        "workload": "96 periodic 2D vortex grids, sides U{128..1024}, beta U[1,5], FP64, 3 fused stages per step",
         "cells": cells,
         "ms_per_step": round(ms, 4),
         "value": cells / (ms * 1e-3),

@@ -349,7 +349,8 @@ const char* fv_last_error(const fv_ctx* ctx);
  * CFL dt. A step is three fused stage launches that cover all work items of
  * all grids (a work item is a 60-column x seg-row piece of one grid, one
  * wavefront each); the three launches are captured once in a HIP graph and
- * replayed per step on the caller's stream.
+ * replayed per step on the caller's stream (batches of large grids are launched
+ * in groups: fv_batch_create).
  * ------------------------------------------------------------------------ */
 typedef struct fv_batch fv_batch;
 
